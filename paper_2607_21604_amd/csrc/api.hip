@@ -1373,7 +1373,7 @@ static akvs_status lm_head_row(const akvs_model_cfg *m, const float *hf, const v
   e.part_val = part_val;
   e.part_idx = part_idx;
   LAUNCH(AKVS_K_GEMV, launch_gemv(hf, AKVS_F32, w_out, m->dtype, m->vocab, m->d_model, e, stream));
-  if (token) LAUNCH(AKVS_K_OTHER, launch_pick(part_val, part_idx, gemv_blocks(m->vocab), token, stream));
+  if (token) LAUNCH(AKVS_K_OTHER, launch_pick(part_val, part_idx, gemv_blocks(m->vocab), 1, token, stream));
   return AKVS_OK;
 }
 
@@ -1396,7 +1396,20 @@ akvs_status akvs_lm_head(const float *h, int32_t n_rows, const void *w_out,
   const size_t need = carve_decode(nullptr, m, 1, b);
   REQUIRE(ws && ws_bytes >= need, AKVS_ENOSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
   carve_decode(ws, m, 1, b);
-  for (int r = 0; r < n_rows; ++r) {
+  // Several rows of a bf16 model go together where their partials fit the one-row layout
+  // (a part_val entry per 8 vocabulary rows), which small vocabularies do not.
+  int sub, r = 0;
+  const int hb = head_rows_blocks(m->vocab, gemm_cu_count(), &sub);
+  const int most = std::min(HEAD_ROWS_MAX, gemv_blocks(m->vocab) / hb);
+  while (m->dtype == AKVS_BF16 && most > 1 && n_rows - r > 1) {
+    const int n = std::min(most, n_rows - r);
+    LAUNCH(AKVS_K_GEMV,
+           launch_head_rows(h + (size_t)r * m->d_model, n, w_out, m->vocab, m->d_model,
+                            logits ? logits + (size_t)r * m->vocab : nullptr, b.part_val,
+                            b.part_idx, tokens ? tokens + r : nullptr, stream));
+    r += n;
+  }
+  for (; r < n_rows; ++r) {
     float *lg = logits ? logits + (size_t)r * m->vocab : b.logits;
     st = lm_head_row(m, h + (size_t)r * m->d_model, w_out, lg, b.part_val, b.part_idx,
                      tokens ? tokens + r : nullptr, stream);

@@ -166,7 +166,6 @@ int gemv_blocks(int N);
 constexpr int GEMV_NORM_MAX = 16384;
 hipError_t launch_gemv(const void *x, int x_dtype, const void *W, int w_dtype, int N, int K,
                        const GemvEpi &e, hipStream_t s);
-// *out = index of the best of n (value, index) partials; -1 if none is a number.
 // Attention of one new row (bf16, hd 64 or 128, hq / hkv <= 8) over n_keys cached keys:
 // per (KV head, key chunk) partials part_o [n_chunks][hq][hd] and part_ml [n_chunks][hq][2]
 // (fp32), merged into out [hq][hd] by a second kernel.
@@ -174,7 +173,15 @@ int decode_attn_chunks(int n_keys, int hkv, int *chunk_keys);
 hipError_t launch_attention_decode(const void *q, const void *k, const void *v, int n_keys,
                                    int hq, int hkv, int hd, void *out, float *part_o,
                                    float *part_ml, hipStream_t s);
-hipError_t launch_pick(const float *part_val, const int32_t *part_idx, int n, int32_t *out,
-                       hipStream_t s);
+// out[r] = index of the best of row r's n (value, index) partials; -1 if none is a number.
+hipError_t launch_pick(const float *part_val, const int32_t *part_idx, int n, int rows,
+                       int32_t *out, hipStream_t s);
+// logits[r] = h[r] . W^T (may be null) and greedy tokens[r] (may be null) of 1..HEAD_ROWS_MAX
+// fp32 rows against bf16 W [V][D], D a multiple of 64, in one read of W. part_val / part_idx:
+// rows * head_rows_blocks(V) entries.
+constexpr int HEAD_ROWS_MAX = 32;
+int head_rows_blocks(int V, int cus, int *sub);
+hipError_t launch_head_rows(const float *h, int rows, const void *W, int V, int D, float *logits,
+                            float *part_val, int32_t *part_idx, int32_t *tokens, hipStream_t s);
 
 }  // namespace akvs

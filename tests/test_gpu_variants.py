@@ -1,5 +1,5 @@
 """Parity of the size- and alignment-dependent kernel variants at the edges of their ranges:
-the wide quantiser against the oracle at ties."""
+the wide quantiser against the oracle at ties, the LM head over several rows."""
 import numpy as np
 import pytest
 import torch
@@ -57,3 +57,52 @@ def test_quantise_codes_at_ties(bits, rows, hd):
             akvs.akvs_quantize_cache(xd, rows, hd, bits, c, mt)
             np.testing.assert_array_equal(c.cpu().numpy(), codes)
             np.testing.assert_array_equal(mt.cpu().numpy().view(np.uint16), meta.view(np.uint16))
+
+
+@pytest.mark.parametrize("rows", [1, 2, 16, 17, 33])
+@pytest.mark.parametrize("vocab,d", [(1021, 192), (160, 64), (1000, 320)])
+def test_lm_head_rows(rows, vocab, d):
+    """Several rows in one call: fp32 logits (error bound of a K-term fp32 sum in any order,
+    K 2^-24 sum |h w|), picks of the lowest index on ties, with and without logits."""
+    sh = synthetic.ModelShape("head", 1, d, 2, 2, 64, 128, vocab, 1e4)
+    m = akvs.model_cfg(sh)
+    h = torch.from_numpy(synthetic.random_array((rows, d), 3 + rows)).float()
+    w = torch.from_numpy(synthetic.random_array((vocab, d), 5 + vocab) * 0.02).to(torch.bfloat16)
+    ref = f64(h) @ f64(w).T
+    bound = d * 2.0 ** -24 * (np.abs(f64(h)) @ np.abs(f64(w)).T)
+    w[vocab - 1] = w[int(ref[0].argmax())]  # row 0's best logit twice: the lower index wins
+    ref = f64(h) @ f64(w).T
+    hd, wd = to_dev(h), to_dev(w)
+    ws = torch.empty(akvs.akvs_decode_workspace_size(m, 0), dtype=torch.uint8, device=DEV)
+    logits = torch.full((rows, vocab), float("nan"), device=DEV)
+    toks = torch.full((rows,), -7, dtype=torch.int32, device=DEV)
+    akvs.akvs_lm_head(hd, rows, wd, m, logits, toks, ws)
+    got = f64(logits)
+    assert np.all(np.abs(got[:, :vocab - 1] - ref[:, :vocab - 1]) <= bound[:, :vocab - 1])
+    np.testing.assert_array_equal(toks.cpu().numpy(), got.argmax(axis=1))
+    only = torch.full((rows,), -7, dtype=torch.int32, device=DEV)
+    akvs.akvs_lm_head(hd, rows, wd, m, None, only, ws)
+    assert torch.equal(only, toks)
+
+
+def test_lm_head_rows_infinities_and_nan():
+    """Infinite weights and rows holding an infinity or a NaN: the values of the plain sums;
+    NaN never wins the pick, a row of NaN picks nothing."""
+    sh = synthetic.ModelShape("head", 1, 64, 2, 2, 64, 128, 300, 1e4)
+    m = akvs.model_cfg(sh)
+    h = torch.from_numpy(synthetic.random_array((4, 64), 9)).float()
+    w = torch.from_numpy(synthetic.random_array((300, 64), 10)).to(torch.bfloat16)
+    h[0, 5] = 1.0  # exactly one bf16 value: the split's other terms are 0
+    w[17, 5] = float("inf")
+    h[1, 3], h[2, 3] = float("inf"), float("nan")
+    ref = (h.double() @ w.double().T).numpy()
+    ws = torch.empty(akvs.akvs_decode_workspace_size(m, 0), dtype=torch.uint8, device=DEV)
+    logits = torch.empty((4, 300), device=DEV)
+    toks = torch.empty(4, dtype=torch.int32, device=DEV)
+    akvs.akvs_lm_head(to_dev(h), 4, to_dev(w), m, logits, toks, ws)
+    got = f64(logits)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+    fin = np.isfinite(ref)
+    np.testing.assert_allclose(got[fin], ref[fin], rtol=0, atol=1e-4)
+    np.testing.assert_array_equal(got[~fin & ~np.isnan(ref)], ref[~fin & ~np.isnan(ref)])
+    assert toks[0].item() == 17 and toks[2].item() == -1
