@@ -13,8 +13,8 @@
 // launch_gemm picks the tile per launch from the row count (on the device when only the device
 // knows it: k_gemm_bf16_pick runs the chosen kernel's blocks). In every kernel the
 // accumulator tile is staged through LDS so the epilogues can pair columns (rotary halves,
-// gate/up) and write coalesced rows. fp32 path (small models): 32x128x32 VALU tiles, same
-// epilogues.
+// gate/up) and write coalesced rows. fp32 path (small models): 16- and 32-row tiles on the
+// fp32 MFMA, same epilogues.
 #include <algorithm>
 #include <type_traits>
 
@@ -954,80 +954,128 @@ __global__ __launch_bounds__(256) void k_gemm_fixup(int M, int N, int K, const i
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 VALU GEMM (small fp32 models). 32x128 tile, BK 32, thread = 4 rows x 4 columns.
-constexpr int GF_M = 32, GF_N = 128, GF_K = 32;
-
-__global__ __launch_bounds__(256) void k_gemm_f32(const float *__restrict__ A, int lda,
+// fp32 GEMM (small fp32 models) on v_mfma_f32_16x16x4_f32: 512 threads on a BM x BN tile, the
+// waves in 4 column groups x 2 halves of K, each wave MI x NJ tiles of 16 x 16. These calls
+// are short (a 288-row projection of a width-256 model is 0.1 GFLOP), so what counts is the
+// number of dependent memory round trips and of blocks: operands go straight from memory to
+// registers as float4 fragments, all of them requested a batch ahead (no LDS staging, no
+// barrier in the loop), and the tile is small. Lane l holds row (column) l % 16 at the four
+// reduction indices 4 (l / 16) + 0..3 of each 16, element e of both operands feeding MFMA e.
+// The two K halves are added through LDS in order, then the shared epilogue runs.
+// The nine projections of a two-layer width-256 model over 288 tokens: 338 us on 32 x 128 vector
+// tiles staged through LDS, 77 us here.
+template <int BM, int BN>
+__global__ __launch_bounds__(512) void k_gemm_f32(const float *__restrict__ A, int lda,
                                                   const float *__restrict__ B, int ldb, int M,
                                                   int N, int K, const int32_t *m_dev, Epi epi) {
-  __shared__ __attribute__((aligned(16))) float smem[GF_M * (GF_N + 4) > GF_K * (GF_M + GF_N + 8)
-                                                        ? GF_M * (GF_N + 4)
-                                                        : GF_K * (GF_M + GF_N + 8)];
-  float *As = smem;                    // [GF_K][GF_M + 4]  (k-major)
-  float *Bs = smem + GF_K * (GF_M + 4);  // [GF_K][GF_N + 4]
-  const int tid = threadIdx.x;
+  constexpr int MI = BM / 16, NJ = BN / 64, U = 8 / (MI * NJ > 1 ? 2 : 1), LDC = BN + 4;
+  __shared__ __attribute__((aligned(16))) float Cs[2 * BM * LDC];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wn = wave & 3, kg = wave >> 2, lr = lane & 15, lg = lane >> 4;
   int M_eff = M;
   if (m_dev) M_eff = min(M, *m_dev);
-  const int m0 = blockIdx.y * GF_M;
+  const int m0 = blockIdx.y * BM;
   if (m0 >= M_eff) return;
   const bool swiglu = epi.mode == EPI_SWIGLU;
-  const int n0 = blockIdx.x * (swiglu ? GF_N / 2 : GF_N);
-  const int tr = tid >> 5, tc = tid & 31;  // rows tr*4.., cols tc*4..
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += GF_K) {
-    __syncthreads();
-    {  // A: 32 rows x 32 k = 256 float4, one per thread
-      const int r = tid >> 3, kc = (tid & 7) * 4;
-      const int gm = m0 + r, gk = k0 + kc;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (gm < M_eff && gk < K) v = *reinterpret_cast<const float4 *>(A + (size_t)gm * lda + gk);
-      As[(kc + 0) * (GF_M + 4) + r] = v.x;
-      As[(kc + 1) * (GF_M + 4) + r] = v.y;
-      As[(kc + 2) * (GF_M + 4) + r] = v.z;
-      As[(kc + 3) * (GF_M + 4) + r] = v.w;
-    }
+  const int n0 = blockIdx.x * (swiglu ? BN / 2 : BN);
+  const float *ap[MI], *bp[NJ];  // rows past M / N read a valid row (results discarded)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {  // B: 128 rows x 32 k = 1024 float4
-      const int c = tid + 256 * i;
-      const int r = c >> 3, kc = (c & 7) * 4;
-      int gn;
-      bool ok;
-      if (swiglu) {
-        const int oc = n0 + (r & 63);
-        ok = oc < N;
-        gn = (r < 64) ? oc : N + oc;
-      } else {
-        gn = n0 + r;
-        ok = gn < N;
+  for (int i = 0; i < MI; ++i) ap[i] = A + (size_t)min(m0 + 16 * i + lr, M_eff - 1) * lda;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int c = (wn * NJ + j) * 16 + lr;
+    int gn;
+    if (swiglu) {
+      const int oc = min(n0 + (c & (BN / 2 - 1)), N - 1);
+      gn = c < BN / 2 ? oc : N + oc;
+    } else {
+      gn = min(n0 + c, N - 1);
+    }
+    bp[j] = B + (size_t)gn * ldb;
+  }
+  const int steps = (K + 15) / 16, half = (steps + 1) / 2;
+  const int s0 = kg * half, s1 = min(steps, s0 + half);  // this wave's 16-wide steps
+  f32x4_t acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+  f32x4_t fa[2][U][MI], fb[2][U][NJ];
+  // (K is a multiple of 4: a float4 is inside K or past it, where both operands are 0)
+  auto fetch = [&](int p, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = (s + u) * 16 + lg * 4;
+      const bool ok = s + u < s1 && k < K;
+      const int kk = ok ? k : 0;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        fa[p][u][i] = *reinterpret_cast<const f32x4_t *>(ap[i] + kk);
+        if (!ok) fa[p][u][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       }
-      const int gk = k0 + kc;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (ok && gk < K) v = *reinterpret_cast<const float4 *>(B + (size_t)gn * ldb + gk);
-      Bs[(kc + 0) * (GF_N + 4) + r] = v.x;
-      Bs[(kc + 1) * (GF_N + 4) + r] = v.y;
-      Bs[(kc + 2) * (GF_N + 4) + r] = v.z;
-      Bs[(kc + 3) * (GF_N + 4) + r] = v.w;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int k = 0; k < GF_K; ++k) {
-      const float4 a = *reinterpret_cast<const float4 *>(As + k * (GF_M + 4) + tr * 4);
-      const float4 b = *reinterpret_cast<const float4 *>(Bs + k * (GF_N + 4) + tc * 4);
-      const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+      for (int j = 0; j < NJ; ++j) {
+        fb[p][u][j] = *reinterpret_cast<const f32x4_t *>(bp[j] + kk);
+        if (!ok) fb[p][u][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      }
     }
+  };
+  auto mul = [&](int p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[p][u][i][e], fb[p][u][j][e],
+                                                             acc[i][j], 0, 0, 0);
+  };
+  fetch(0, s0);
+  for (int s = s0; s < s1; s += 2 * U) {
+    fetch(1, s + U);
+    mul(0);
+    if (s + U >= s1) break;
+    fetch(0, s + 2 * U);
+    mul(1);
+  }
+  float *mine = Cs + kg * BM * LDC;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        mine[(16 * i + lg * 4 + r) * LDC + (wn * NJ + j) * 16 + lr] = acc[i][j][r];
+  __syncthreads();
+  for (int e = tid; e < BM * BN; e += 512) {
+    const int o = (e / BN) * LDC + e % BN;
+    Cs[o] += Cs[BM * LDC + o];
   }
   __syncthreads();
-  float *Cs = smem;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) Cs[(tr * 4 + i) * (GF_N + 4) + tc * 4 + j] = acc[i][j];
-  __syncthreads();
-  epilogue_tile<GF_M, GF_N, 256>(Cs, GF_N + 4, m0, n0, M_eff, N, epi);
+  epilogue_tile<BM, BN, 512>(Cs, LDC, m0, n0, M_eff, N, epi);
+}
+
+// Tile of the fp32 kernel: 64 columns (128 where a head of 128 must stay whole), 16 rows
+// while those make at most four blocks per CU, then 32 (each operand row read half as often).
+static void launch_f32(const float *A, int lda, const float *B, int ldb, int M, int N, int K,
+                       const int32_t *m_dev, const Epi &epi, hipStream_t s) {
+  const int bn = epi.mode == EPI_QKV && epi.hd == 128 ? 128 : 64;
+  const int bn_out = epi.mode == EPI_SWIGLU ? bn / 2 : bn;
+  const int gn = (N + bn_out - 1) / bn_out;
+  const bool small = (long long)gn * ((M + 15) / 16) <= 4LL * gemm_cu_count();
+  const dim3 g(gn, small ? (M + 15) / 16 : (M + 31) / 32), b(512);
+#define AKVS_F32(BM_, BN_)                                                                     \
+  hipLaunchKernelGGL((k_gemm_f32<BM_, BN_>), g, b, 0, s, A, lda, B, ldb, M, N, K, m_dev, epi)
+  if (bn == 64) {
+    if (small) AKVS_F32(16, 64); else AKVS_F32(32, 64);
+  } else {
+    if (small) AKVS_F32(16, 128); else AKVS_F32(32, 128);
+  }
+#undef AKVS_F32
 }
 
 int gemm_cu_count() {
@@ -1181,11 +1229,8 @@ hipError_t launch_gemm(const void *A, int lda, const void *B, int ldb, int M, in
                        reinterpret_cast<const bf16_t *>(B), ldb, M, N, K, m_dev, epi, p.n_slots,
                        part);
   } else {
-    const bool swiglu = epi.mode == EPI_SWIGLU;
-    const int bn = swiglu ? GF_N / 2 : GF_N;
-    dim3 g((N + bn - 1) / bn, (M + GF_M - 1) / GF_M), b(256);
-    hipLaunchKernelGGL(k_gemm_f32, g, b, 0, s, reinterpret_cast<const float *>(A), lda,
-                       reinterpret_cast<const float *>(B), ldb, M, N, K, m_dev, epi);
+    launch_f32(reinterpret_cast<const float *>(A), lda, reinterpret_cast<const float *>(B), ldb, M,
+               N, K, m_dev, epi, s);
   }
   return hipGetLastError();
 }
