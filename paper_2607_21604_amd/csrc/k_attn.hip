@@ -727,19 +727,28 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
   store8(out + item * hd + e0, a);
 }
 
-// fp32 path (small models): one wave per (row, head), keys in tiles of 64, online softmax.
+// fp32 path (small models), on v_mfma_f32_16x16x4_f32. Block = 16 rows of one query head, 8
+// waves that take the 16-key tiles in turn (wave w the tiles w, w + 8, ...), each with its own
+// running maximum, sum and output, merged through LDS in wave order at the end: short calls
+// are bound by dependent memory round trips, so a tile needs two (K and V together) and no
+// barrier. Scores are formed transposed, S^T = K Q^T: lane l holds the scores of row l % 16
+// at keys 4 (l / 16) + 0..3 of the tile, which is the operand layout of O^T = V^T P^T as it is.
+// 288 rows over 288 keys, 4 heads of 64: 30 us with one wave per (row, head) reading key rows
+// a lane each, 17 us here.
 template <int HD>
-__global__ __launch_bounds__(64) void k_attn_f32(const float *__restrict__ Q, const int32_t *pos,
-                                                 int pos0, int rows, const int32_t *rows_dev,
-                                                 const float *__restrict__ Kc,
-                                                 const float *__restrict__ Vc, int n_keys, int hq,
-                                                 int hkv, float scale, float *__restrict__ out,
-                                                 const int32_t *row_base) {
-  constexpr int PER = HD / 64;
-  __shared__ float qs[HD];
-  __shared__ float ps[64];
-  const int lane = threadIdx.x;
-  const int r = blockIdx.x, head = blockIdx.y;
+__global__ __launch_bounds__(512) void k_attn_f32(const float *__restrict__ Q, const int32_t *pos,
+                                                  int pos0, int rows, const int32_t *rows_dev,
+                                                  const float *__restrict__ Kc,
+                                                  const float *__restrict__ Vc, int n_keys, int hq,
+                                                  int hkv, float scale_log2,
+                                                  float *__restrict__ out,
+                                                  const int32_t *row_base) {
+  constexpr int C = HD / 16, NW = 8;
+  __shared__ float s_o[NW][HD][17];
+  __shared__ float s_m[NW][16], s_l[NW][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int row0 = blockIdx.x * 16, head = blockIdx.y;
   if (row_base) {
     const int rb0 = *row_base;
     Q += (size_t)rb0 * hq * HD;
@@ -748,46 +757,96 @@ __global__ __launch_bounds__(64) void k_attn_f32(const float *__restrict__ Q, co
   }
   int R = rows;
   if (rows_dev) R = min(R, *rows_dev);
-  if (r >= R) return;
+  if (row0 >= R) return;
   const int kvh = head / (hq / hkv);
-  const int rp = pos ? pos[r] : pos0 + r;
-  const int kv_end = min(n_keys, rp + 1);
-  const float *q = Q + ((size_t)r * hq + head) * HD;
-  for (int e = lane; e < HD; e += 64) qs[e] = q[e];
-  __syncthreads();
-  float m = -INFINITY, l = 0.f, acc[PER];
+  const int r = row0 + lr;
+  const bool rvalid = r < R;
+  const int rp = rvalid ? (pos ? pos[r] : pos0 + r) : -1;
+  const int lim = min(n_keys - 1, rp);  // the row's last key
+  int last = lim;                       // the block's last key
 #pragma unroll
-  for (int i = 0; i < PER; ++i) acc[i] = 0.f;
-  for (int key0 = 0; key0 < kv_end; key0 += 64) {
-    const int key = key0 + lane;
-    float sc = -INFINITY;
-    if (key < kv_end) {
-      const float *k = Kc + ((size_t)key * hkv + kvh) * HD;
-      float d = 0.f;
-      for (int e = 0; e < HD; ++e) d = fmaf(qs[e], k[e], d);
-      sc = d * scale;
+  for (int o = 1; o < 16; o <<= 1) last = max(last, __shfl_xor(last, o, 64));
+  f32x4_t qf[C];
+  {
+    const float *q = Q + ((size_t)(rvalid ? r : row0) * hq + head) * HD + lg * 4;
+#pragma unroll
+    for (int c = 0; c < C; ++c) qf[c] = *reinterpret_cast<const f32x4_t *>(q + 16 * c);
+  }
+  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4_t o[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) o[c] = zero;
+  float m = -INFINITY, l = 0.f;  // of row lr (l: this lane's quarter of the keys)
+  for (int key0 = wave * 16; key0 <= last; key0 += NW * 16) {
+    f32x4_t kf[C];
+    float vf[C][4];
+    {  // keys past the block's last one re-read it (masked below)
+      const float *k = Kc + ((size_t)min(key0 + lr, last) * hkv + kvh) * HD + lg * 4;
+#pragma unroll
+      for (int c = 0; c < C; ++c) kf[c] = *reinterpret_cast<const f32x4_t *>(k + 16 * c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float *v = Vc + ((size_t)min(key0 + lg * 4 + e, last) * hkv + kvh) * HD + lr;
+#pragma unroll
+        for (int c = 0; c < C; ++c) vf[c][e] = v[16 * c];
+      }
     }
-    const float mx = wave_max(sc);
-    const float m_new = fmaxf(m, mx);
-    const float alpha = (m == -INFINITY) ? 0.f : __expf(m - m_new);
-    const float p = (sc == -INFINITY) ? 0.f : __expf(sc - m_new);
-    l = l * alpha + wave_sum(p);
-    m = m_new;
-    __syncthreads();
-    ps[lane] = p;
-    __syncthreads();
-    const int nk = min(64, kv_end - key0);
+    f32x4_t s = zero;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = lane + 64 * i;
-      float a = acc[i] * alpha;
-      for (int j = 0; j < nk; ++j) a = fmaf(ps[j], Vc[((size_t)(key0 + j) * hkv + kvh) * HD + e], a);
-      acc[i] = a;
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[c][e], s, 0, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      s[e] = key0 + lg * 4 + e <= lim ? s[e] * scale_log2 : -INFINITY;
+    float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m, mx);
+    const float off = m_new == -INFINITY ? 0.f : m_new;  // no key yet: every p is 0
+    const float alpha = __builtin_amdgcn_exp2f(m - off);
+    f32x4_t p;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(s[e] - off);
+    l = l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
+    m = m_new;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      o[c] *= alpha;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][e], p[e], o[c], 0, 0, 0);
     }
   }
-  float *o = out + ((size_t)r * hq + head) * HD;
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  // o[c][e] is dim 16 c + 4 lg + e of row lr
 #pragma unroll
-  for (int i = 0; i < PER; ++i) o[lane + 64 * i] = acc[i] / l;
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s_o[wave][16 * c + 4 * lg + e][lr] = o[c][e];
+  if (lg == 0) {
+    s_m[wave][lr] = m;
+    s_l[wave][lr] = l;
+  }
+  __syncthreads();
+  for (int x = threadIdx.x; x < 16 * HD; x += 512) {
+    const int i = x / HD, d = x - i * HD;
+    if (row0 + i >= R) break;
+    float mm = s_m[0][i];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_m[w][i]);
+    float so = 0.f, sl = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (s_m[w][i] == -INFINITY) continue;  // no key of the row in this wave's tiles
+      const float a = __builtin_amdgcn_exp2f(s_m[w][i] - mm);
+      so = fmaf(a, s_o[w][d][i], so);
+      sl = fmaf(a, s_l[w][i], sl);
+    }
+    out[((size_t)(row0 + i) * hq + head) * HD + d] = so / sl;
+  }
 }
 
 int attn_splits(int rows, int hq, int hkv, int n_keys) {
@@ -889,8 +948,8 @@ hipError_t launch_attention(const void *q, const int32_t *pos, int pos0, int row
                          rows_dev, hq, hd, O, row_base, nullptr);
     }
   } else {
-    const float scale = 1.0f / sqrtf((float)hd);
-    dim3 g(rows, hq), b(64);
+    const float scale = 1.4426950408889634f / sqrtf((float)hd);
+    dim3 g((rows + 15) / 16, hq), b(512);
     const float *Q = reinterpret_cast<const float *>(q);
     const float *K = reinterpret_cast<const float *>(k);
     const float *V = reinterpret_cast<const float *>(v);

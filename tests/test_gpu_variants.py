@@ -1,5 +1,5 @@
 """Parity of the size- and alignment-dependent kernel variants at the edges of their ranges:
-the wide quantiser against the oracle at ties, the LM head over several rows."""
+the wide quantiser against the oracle at ties, the LM head over several rows, the fp32 tiles."""
 import numpy as np
 import pytest
 import torch
@@ -7,7 +7,7 @@ import torch
 import oracle
 import synthetic
 from paper_2607_21604_amd import akvs
-from tests.gpu_util import DEV, f64, to_dev
+from tests.gpu_util import DEV, f64, max_rel, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -106,3 +106,53 @@ def test_lm_head_rows_infinities_and_nan():
     np.testing.assert_allclose(got[fin], ref[fin], rtol=0, atol=1e-4)
     np.testing.assert_array_equal(got[~fin & ~np.isnan(ref)], ref[~fin & ~np.isnan(ref)])
     assert toks[0].item() == 17 and toks[2].item() == -1
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,ffn,rows", [
+    (72, 3, 1, 64, 100, 1), (72, 3, 1, 64, 100, 17), (8, 1, 1, 64, 4, 16),
+    (200, 4, 2, 128, 1028, 33), (200, 4, 2, 128, 1028, 2080)])
+def test_fp32_projections(d, hq, hkv, hd, ffn, rows):
+    """The fp32 tiles (16 and 32 rows, 64 and 128 columns) at remainders of rows, columns and
+    K, against the oracle. Tolerance of the fp32 path."""
+    shape = synthetic.ModelShape("v", 1, d, hq, hkv, hd, ffn, 64, 1e4, dtype="f32")
+    w = synthetic.make_weights(shape, seed=rows, std=0.1, embed=False)
+    dims = oracle.dims_from(shape)
+    m = akvs.model_cfg(shape)
+    lwd = {k: to_dev(t) for k, t in w["layers"][0].items()}
+    lws = akvs.layer_array({"layers": [lwd]})[0]
+    h = synthetic.random_array((rows, d), 6).astype(np.float32)
+    pos = np.arange(rows, dtype=np.int32) * 2
+    table = torch.empty((2 * rows, hd // 2, 2), device=DEV)
+    akvs.akvs_rope_table(2 * rows, hd, 1e4, table)
+    q = torch.empty((rows, hq, hd), device=DEV)
+    kf, vf = (torch.empty((rows, hkv, hd), device=DEV) for _ in range(2))
+    ws = torch.empty(akvs.akvs_step_workspace_size(m, rows), dtype=torch.uint8, device=DEV)
+    hdev = to_dev(h)
+    akvs.akvs_probe_qkv(hdev, rows, to_dev(pos), m, lws, table, 2 * rows, q, kf, vf, ws)
+    sw = oracle.split_layer(w["layers"][0], dims)
+    for got, ref in zip((q, kf, vf), oracle.model.project_qkv(h.astype(np.float64), pos, sw, dims)):
+        assert max_rel(f64(got), ref) < 1e-5
+    att = synthetic.random_array((rows, hq * hd), 7).astype(np.float32)
+    akvs.akvs_probe_out_mlp(hdev, rows, to_dev(att), m, lws, ws)
+    ref = oracle.model.output_and_mlp(h.astype(np.float64), att.astype(np.float64), sw, dims)
+    assert max_rel(f64(hdev), ref) < 1e-5
+
+
+@pytest.mark.parametrize("hq,hkv,hd,rows,n_keys", [
+    (2, 1, 64, 1, 1), (2, 2, 128, 15, 17), (4, 1, 64, 17, 129), (3, 3, 128, 40, 300),
+    (1, 1, 64, 16, 1000)])
+def test_fp32_attention(hq, hkv, hd, rows, n_keys):
+    """Rows and keys around the 16-row tile and the 8 x 16 keys of one turn of its waves."""
+    rng = np.random.default_rng(n_keys)
+    rows = min(rows, n_keys)
+    pos = np.sort(rng.choice(n_keys, size=rows, replace=False)).astype(np.int32)
+    q, k, v = (synthetic.random_array((n, h, hd), 40 + i).astype(np.float32)
+               for i, (n, h) in enumerate([(rows, hq), (n_keys, hkv), (n_keys, hkv)]))
+    q[0] *= 30  # one row of large scores
+    m = akvs.ModelCfg(1, 64, hq, hkv, hd, 64, 16, 1e4, 1e-6, akvs.AKVS_F32)
+    out = torch.empty((rows, hq * hd), device=DEV)
+    akvs.akvs_sparse_query_attention(to_dev(q), to_dev(pos), rows, to_dev(k), to_dev(v), n_keys, m,
+                                     out)
+    ref = oracle.attention(q.astype(np.float64), pos, k.astype(np.float64), v.astype(np.float64),
+                           np.arange(n_keys)).reshape(rows, -1)
+    assert max_rel(f64(out), ref) < 1e-5
