@@ -2,12 +2,13 @@
 // epilogues: RoPE + q/k/v split (QKV), residual add into the fp32 stream (RESID),
 // SiLU(gate) * up (SWIGLU) and plain stores.
 //
-// bf16 path, three kernels on v_mfma_f32_32x32x16_bf16 with fp32 accumulation, operand
+// bf16 path, four kernels on v_mfma_f32_32x32x16_bf16 with fp32 accumulation, operand
 // tiles double-buffered in LDS and fed by register stages of global loads:
-//   k_gemm_bf16_w8 - 8 waves, BM x BN x 64 tiles (256/192 x 256/128), all waves on one
+//   k_gemm_bf16_w8 - 8 waves, BM x BN x 64 tiles (256/192/128 x 256/128), all waves on one
 //                    schedule interleaving loads, LDS stores and MFMAs;
 //   k_gemm_bf16_pp - 8 waves, 192 x 256 tiles, two wave groups alternating memory and
 //                    MFMA phases ("ping-pong");
+//   k_gemm_few     - few rows (k_few.hip): small tiles, operands straight into LDS;
 //   k_gemm_bf16    - 4 waves, 128 x 128 tiles, with the K split (and its fixup pass) for
 //                    grids too small to fill the GPU and for operands past 2 GiB.
 // launch_gemm picks the tile per launch from the row count (on the device when only the device
@@ -18,15 +19,10 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "gemm_dev.h"
 #include "kernels.h"
 
 namespace akvs {
-
-// g * sigmoid(g) with the hardware reciprocal (v_rcp_f32, 1 ulp) in place of an IEEE
-// division, which cost about twice the instructions of the rest of the SwiGLU epilogue
-__device__ __forceinline__ float silu(float g) {
-  return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
-}
 
 // Epilogue over an LDS tile Cs[BM][ldc] holding C[m0.., n0..] (SWIGLU: gate cols [0,BN/2),
 // up cols [BN/2,BN) of output columns n0..n0+BN/2). Thread tid takes items tid + it * NT.
@@ -408,7 +404,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_bf16(const bf16_t *__restrict__
 
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA GEMM with 8 waves: 512-thread blocks (two waves per SIMD) on BM x BN x 64 block
-// tiles, BM in {192, 256}, BN in {128, 256}. Waves form WGM x (8 / WGM), each owning
+// tiles, BM in {128, 192, 256}, BN in {128, 256}. Waves form WGM x (8 / WGM), each owning
 // (BM / WGM) x (BN * WGM / 8) outputs as v_mfma_f32_32x32x16_bf16 tiles. Against 128x128
 // tiles of four waves this halves the operand bytes per flop while keeping two waves per
 // SIMD. Operands arrive through buffer loads into NST register stages; each k-tile's LDS
@@ -419,30 +415,6 @@ __global__ __launch_bounds__(256, 2) void k_gemm_bf16(const bf16_t *__restrict__
 // to valid rows (their results are discarded). The B row count (2N for SWIGLU) arrives as a
 // kernel argument: derived on the device from the epilogue mode, the compiler keeps it in a
 // vector register and wraps every B load in a loop over distinct descriptors.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_rsrc(const void *p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes,
-                                           0x00020000);
-}
-
-
-// Output tile of block b: blocks past the live tile count exit; the live blocks are spread
-// so that each XCD (blocks b, b+8, ... of the dispatch order) takes one contiguous run of
-// the logical tile order, and the logical order walks groups of GM row tiles, rows fastest,
-// so that the blocks resident on one XCD share a few A and B panels in its L2.
-template <int GM>
-__device__ __forceinline__ bool grouped_tile(int b, int m_tiles, int n_tiles, int &mt, int &nt) {
-  const int live = m_tiles * n_tiles;
-  if (b >= live) return false;
-  const int x = b & 7, idx = b >> 3;
-  const int base = live >> 3, extra = live & 7;
-  const int t = x * base + min(x, extra) + idx;
-  const int per_group = GM * n_tiles;
-  const int g = t / per_group, local = t - g * per_group;
-  const int rows = min(GM, m_tiles - g * GM);
-  mt = g * GM + local % rows;
-  nt = local / rows;
-  return true;
-}
 
 template <int BM, int BN, int WGM, int NST>
 struct Gemm8 {
@@ -804,41 +776,48 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_pp(const bf16_t *__restric
   gemm_pp_body<BM, BN>(smem, blockIdx.x, A, lda, B, ldb, M_eff, N, K, b_rows, epi);
 }
 
-// Block tiles of the 8-wave kernels with their rate per CU relative to the 256x256 tile,
-// measured on the 3B projection shapes with every CU busy (M = 1405 and 4516 rows). A launch
-// takes the tile with the least (rounds of one tile per CU) x (tile area) / rate at its row
-// count. The ping-pong kernel needs long compute phases: only its 192x256 tile was kept
-// (with 128 columns per tile a phase holds 12 MFMAs and the shared schedule is faster; at
-// 192x256 the shared schedule measured 0.75 against the ping-pong's 0.88). Checked on the
-// 7B and 32B projection shapes with the clocks warmed up: the model's pick was the fastest
-// tile or within a few percent of it.
+// Block tiles of the 8-wave kernels with the cost of one tile: its area over its rate per CU
+// relative to the 256x256 tile (1.0, 0.88, 0.78, 0.74, 0.78, 0.68), measured on the 3B
+// projection shapes. A launch takes the tile with the least (rounds of one tile per CU) x cost
+// at its row count; whole numbers, so that host and device agree on every pick. The ping-pong
+// kernel needs long compute phases: only its 192x256 tile was kept (with 128 columns per tile a
+// phase holds 12 MFMAs and the shared schedule is faster; at 192x256 the shared schedule
+// measured 0.75 against the ping-pong's 0.88). Checked on the 7B and 32B projection shapes with
+// the clocks warmed up: the model's pick was the fastest tile or within a few percent of it.
+// 128-row tiles fit row counts that leave the larger ones' last round or last row tile empty
+// (3B output projection at 818 rows: 31.3 us as a K split, 27.6 on 128x128).
 struct W8Tile {
-  int bm, bn;
-  bool pp;
-  float rate;
+  int bm, bn, cost;
 };
-constexpr int kW8Count = 4;
+constexpr int kW8Count = 6;
 __host__ __device__ inline W8Tile w8_tile(int i) {
   switch (i) {
-    case 0: return {256, 256, false, 1.0f};
-    case 1: return {192, 256, true, 0.88f};
-    case 2: return {256, 128, false, 0.78f};
-    default: return {192, 128, false, 0.74f};
+    case 0: return {256, 256, 65536};
+    case 1: return {192, 256, 55855};
+    case 2: return {256, 128, 42010};
+    case 3: return {192, 128, 33211};
+    case 4: return {128, 256, 42010};
+    default: return {128, 128, 24094};
   }
 }
-__host__ __device__ inline int gemm_w8_tile(int M, int N, int mode, int cus) {
+__host__ __device__ inline int w8_tiles(int i, int M, int N, int mode) {
+  const W8Tile c = w8_tile(i);
+  const int bn_out = mode == EPI_SWIGLU ? c.bn / 2 : c.bn;
+  return ((M + c.bm - 1) / c.bm) * ((N + bn_out - 1) / bn_out);
+}
+__host__ __device__ inline int gemm_w8_tile(int M, int N, int mode, int cus,
+                                            long long *cost_out = nullptr) {
   int best = 0;
-  float best_cost = 0;
+  long long best_cost = 0;
   for (int i = 0; i < kW8Count; ++i) {
-    const W8Tile c = w8_tile(i);
-    const int bn_out = mode == EPI_SWIGLU ? c.bn / 2 : c.bn;
-    const int tiles = ((M + c.bm - 1) / c.bm) * ((N + bn_out - 1) / bn_out);
-    const float cost = (float)((tiles + cus - 1) / cus) * (float)(c.bm * c.bn) / c.rate;
+    const long long cost =
+        (long long)((w8_tiles(i, M, N, mode) + cus - 1) / cus) * w8_tile(i).cost;
     if (i == 0 || cost < best_cost) {
       best = i;
       best_cost = cost;
     }
   }
+  if (cost_out) *cost_out = best_cost;
   return best;
 }
 
@@ -864,8 +843,9 @@ __host__ __device__ inline int w8_k_splits(int M, int N, int K, int mode, int cu
 // block of the chosen kernel (blocks past that kernel's item count exit). The grid covers
 // the largest of the grids over the row counts the host cannot rule out.
 constexpr int kPickSmem =
-    std::max(std::max(Gemm8<256, 256, 2, 1>::SMEM, GemmPP<192, 256>::SMEM),
-             std::max(Gemm8<256, 128, 4, 2>::SMEM, Gemm8<192, 128, 2, 2>::SMEM));
+    std::max({Gemm8<256, 256, 2, 1>::SMEM, GemmPP<192, 256>::SMEM, Gemm8<256, 128, 4, 2>::SMEM,
+              Gemm8<192, 128, 2, 2>::SMEM, Gemm8<128, 256, 2, 1>::SMEM,
+              Gemm8<128, 128, 2, 2>::SMEM});
 __global__ __launch_bounds__(512, 1) void k_gemm_bf16_pick(const bf16_t *__restrict__ A, int lda,
                                                            const bf16_t *__restrict__ B, int ldb,
                                                            int M, int N, int K, int b_rows,
@@ -889,8 +869,14 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_pick(const bf16_t *__restr
     case 2:
       gemm_w8_body<256, 128, 4, 2>(smem, blockIdx.x, A, lda, B, ldb, M_eff, N, K, b_rows, epi);
       break;
-    default:
+    case 3:
       gemm_w8_body<192, 128, 2, 2>(smem, blockIdx.x, A, lda, B, ldb, M_eff, N, K, b_rows, epi);
+      break;
+    case 4:
+      gemm_w8_body<128, 256, 2, 1>(smem, blockIdx.x, A, lda, B, ldb, M_eff, N, K, b_rows, epi);
+      break;
+    default:
+      gemm_w8_body<128, 128, 2, 2>(smem, blockIdx.x, A, lda, B, ldb, M_eff, N, K, b_rows, epi);
       break;
   }
 }
@@ -1165,29 +1151,122 @@ static void launch_pp(const void *A, int lda, const void *B, int ldb, int M, int
 
 // The 8-wave launch for one row-count range: the tile (and K split) every count in
 // [lo, M] picks, or -1 when they differ (the device then picks); any_split when some count
-// in the range splits K.
+// in the range splits K; items: the most blocks that any count up to M makes live. (A grid as large
+// as every tile of the menu may need cost 5 % on the 3B QKV and gate/up projections at 1667
+// rows: each block past the live ones still takes a CU's LDS to find that out.)
 struct W8Choice {
   int choice;  // kernel index of w8_tile, 100 + splits for the split 192x128 tile, -1 mixed
   bool any_split;
+  int items;
 };
 static W8Choice w8_choice(int M, int N, int K, const int32_t *m_dev, int mode,
                           const float *part, int m_min) {
   const int cus = gemm_cu_count();
-  auto at = [&](int m) {
+  W8Choice c{0, false, 0};
+  const int lo = m_dev ? std::min(std::max(m_min, 1), M) : M;
+  // every tile's row count is a multiple of 64: all counts in (64 k, 64 k + 64] act alike
+  bool first = true;
+  int whole = 0;  // most live blocks where nothing may split
+  for (int m = m_dev ? std::min(64, M) : M;; m = std::min(M, m + 64)) {
     const int sp = part ? w8_k_splits(m, N, K, mode, cus) : 1;
-    return sp > 1 ? 100 + sp : gemm_w8_tile(m, N, mode, cus);
-  };
-  W8Choice c{at(M), false};
-  c.any_split = c.choice >= 100;
-  if (m_dev) {
-    for (int m = std::max(m_min, 1); m < M; m = std::min(M, m + 16)) {
-      const int x = at(m);
-      c.any_split |= x >= 100;
-      if (x != c.choice) c.choice = -1;
+    const int tile = gemm_w8_tile(m, N, mode, cus), x = sp > 1 ? 100 + sp : tile;
+    const int n = w8_tiles(tile, m, N, mode);
+    whole = std::max(whole, n);
+    c.items = std::max(c.items, sp > 1 ? w8_tiles(3, m, N, mode) * sp : n);
+    if (m >= lo) {
+      c.any_split |= sp > 1;
+      c.choice = first || x == c.choice ? x : -1;
+      first = false;
     }
+    if (m == M) break;
   }
+  if (!c.any_split) c.items = whole;
   if (c.any_split) c.choice = -1;  // the split launches go through the picking kernel
   return c;
+}
+
+// The few-row kernel (k_few.hip) or the 8-wave kernels: estimated times in us, from timings of
+// every tile at 24 to 820 rows of the 3B, 7B and 32B projections (median error about 10 %).
+// A launch costs 4 us and, per round of one block per CU, its k-steps of 64 columns times the
+// tile's measured step time; it cannot be shorter than its weights' stream (5.3 TB/s for the
+// few-row kernels' deep request queue, 4.4 over several rounds of them, 4.2 for the 8-wave
+// tiles, 5.3 for 128 x 256, 3.6 when they split K).
+// A K split adds a second launch and the partials' round trip. Examples at 173 rows of the
+// 3B shapes, 8-wave against few-row: QKV 24.3 -> 15.8 us (64 x 64), output 18.4 -> 13.3
+// (64 x 64), gate/up 39.8 -> 34.0 (96 x 128), down 29.7 -> 25.3 (96 x 128, four slices); at
+// 64 rows 21.1 -> 12.2, 17.2 -> 10.0, 37.8 -> 22.8 and 25.6 -> 16.6. From about 500 rows on the
+// 8-wave tiles take over (3B gate/up at 475 rows: 52 against 66 us).
+struct FewTile {
+  int bm, bn, bk;
+  float step;  // us per 64 columns of K, chip full
+};
+constexpr FewTile kFewTiles[] = {
+    {32, 64, 128, 0.20f}, {64, 64, 128, 0.29f}, {96, 64, 128, 0.33f}, {96, 128, 64, 0.56f},
+    {128, 128, 64, 0.65f}};
+constexpr int kFewCount = 5;
+constexpr int kFewMaxRows = 1024;  // the range the step times were measured on
+
+struct FewChoice {
+  int tile;  // -1: the 8-wave kernels
+  int splits;
+};
+
+// Slices of nk k-tiles such that none is empty, from a wanted count.
+static int even_splits(int nk, int want) {
+  const int per = (nk + want - 1) / want;
+  return (nk + per - 1) / per;
+}
+
+static FewChoice few_choice(int M, int N, int K, const int32_t *m_dev, const Epi &epi,
+                            const float *part, int m_min) {
+  FewChoice best{-1, 1};
+  if (M > kFewMaxRows || N % 4 != 0) return best;
+  if (epi.mode != EPI_RESID && (epi.mode == EPI_STORE || epi.out_dtype != AKVS_BF16)) return best;
+  const int cus = gemm_cu_count(), nk64 = K / 64;
+  const bool swiglu = epi.mode == EPI_SWIGLU;
+  // a row count known only on the device lies between the bounds, nearer to the upper one
+  // (two probe sets overlap little): priced at two thirds of the way
+  const int lo = m_dev ? std::min(std::max(m_min, 1), M) : M;
+  const int m = lo + 2 * (M - lo) / 3;
+  const double w_mb = (swiglu ? 2.0 : 1.0) * N * K * 2e-6;
+  auto split_cost = [&](double floats) { return 3.5 + floats * 8e-6 / 6.0; };
+  // the 8-wave kernels
+  long long cost;
+  const int w8 = gemm_w8_tile(m, N, epi.mode, cus, &cost);
+  double t_best = 4 + std::max((double)cost * (1.70 / 65536) * nk64, w_mb / (w8 == 4 ? 5.3 : 4.2));
+  const int w8_sp = part ? w8_k_splits(m, N, K, epi.mode, cus) : 1;
+  if (w8_sp > 1) {
+    const int bn_out = swiglu ? kW8SplitBN / 2 : kW8SplitBN;
+    const double tiles = ((m + kW8SplitBM - 1) / kW8SplitBM) * (double)((N + bn_out - 1) / bn_out);
+    t_best = 4 + std::max((double)((nk64 + w8_sp - 1) / w8_sp) * 0.72, w_mb / 3.6) +
+             split_cost(tiles * w8_sp * kW8SplitBM * kW8SplitBN);
+  }
+  for (int i = 0; i < kFewCount; ++i) {
+    const FewTile &t = kFewTiles[i];
+    if (K % t.bk) continue;
+    const int bn_out = swiglu ? t.bn / 2 : t.bn, nk = K / t.bk;
+    const int tiles = ((m + t.bm - 1) / t.bm) * ((N + bn_out - 1) / bn_out);
+    int last = 0;
+    for (int want = 1; want <= kFewMaxSplits; ++want) {
+      const int sp = even_splits(nk, std::min(want, nk));
+      if (sp == last) continue;
+      last = sp;
+      // slices need partials, which are set aside where the 8-wave kernels may split
+      if (sp > 1 && (epi.mode != EPI_RESID || !part || tiles * sp > cus ||
+                     w8_k_splits(1, N, K, epi.mode, cus) < 2 ||
+                     (size_t)sp * M * N > (size_t)cus * kW8SplitBM * kW8SplitBN))
+        break;
+      const double rounds = (tiles * sp + cus - 1) / cus;
+      const double steps = (double)((nk + sp - 1) / sp) * (t.bk / 64);
+      const double us = 4 + std::max(rounds * steps * t.step, w_mb / (rounds > 1 ? 4.4 : 5.3)) +
+                        (sp > 1 ? split_cost((double)sp * m * N) : 0.0);
+      if (us < t_best) {
+        t_best = us;
+        best = {i, sp};
+      }
+    }
+  }
+  return best;
 }
 
 hipError_t launch_gemm(const void *A, int lda, const void *B, int ldb, int M, int N, int K,
@@ -1199,16 +1278,13 @@ hipError_t launch_gemm(const void *A, int lda, const void *B, int ldb, int M, in
     // buffer offsets are 32-bit: larger operands stay on the 4-wave kernel
     const bool fits = (size_t)M * lda * 2 < (1u << 31) && b_rows * ldb * 2 < (1u << 31);
     if (fits) {
+      const FewChoice f = few_choice(M, N, K, m_dev, epi, part, m_min);
+      if (f.tile >= 0)
+        return launch_few(f.tile, f.splits, A, lda, B, ldb, M, N, K, m_dev, epi, part, s);
       const int cus = gemm_cu_count();
       const W8Choice c = w8_choice(M, N, K, m_dev, epi.mode, part, m_min);
       if (c.choice < 0) {
-        int grid = c.any_split ? cus : 0;
-        for (int i = 0; i < kW8Count; ++i) {
-          const W8Tile t = w8_tile(i);
-          const int bn_out = epi.mode == EPI_SWIGLU ? t.bn / 2 : t.bn;
-          grid = std::max(grid, ((M + t.bm - 1) / t.bm) * ((N + bn_out - 1) / bn_out));
-        }
-        hipLaunchKernelGGL(k_gemm_bf16_pick, dim3(grid), dim3(512), 0, s,
+        hipLaunchKernelGGL(k_gemm_bf16_pick, dim3(c.items), dim3(512), 0, s,
                            reinterpret_cast<const bf16_t *>(A), lda,
                            reinterpret_cast<const bf16_t *>(B), ldb, M, N, K,
                            epi.mode == EPI_SWIGLU ? 2 * N : N, m_dev, epi, cus,
@@ -1219,7 +1295,9 @@ hipError_t launch_gemm(const void *A, int lda, const void *B, int ldb, int M, in
         case 0: launch_w8<256, 256, 2, 1>(A, lda, B, ldb, M, N, K, m_dev, epi, s); break;
         case 1: launch_pp<192, 256>(A, lda, B, ldb, M, N, K, m_dev, epi, s); break;
         case 2: launch_w8<256, 128, 4, 2>(A, lda, B, ldb, M, N, K, m_dev, epi, s); break;
-        default: launch_w8<192, 128, 2, 2>(A, lda, B, ldb, M, N, K, m_dev, epi, s); break;
+        case 3: launch_w8<192, 128, 2, 2>(A, lda, B, ldb, M, N, K, m_dev, epi, s); break;
+        case 4: launch_w8<128, 256, 2, 1>(A, lda, B, ldb, M, N, K, m_dev, epi, s); break;
+        default: launch_w8<128, 128, 2, 2>(A, lda, B, ldb, M, N, K, m_dev, epi, s); break;
       }
       return hipGetLastError();
     }
@@ -1242,6 +1320,9 @@ hipError_t launch_gemm_fixup(const void *, int lda, const void *, int ldb, int M
   const size_t b_rows = epi.mode == EPI_SWIGLU ? 2 * (size_t)N : (size_t)N;
   const bool fits = (size_t)M * lda * 2 < (1u << 31) && b_rows * ldb * 2 < (1u << 31);
   if (fits) {
+    const FewChoice f = few_choice(M, N, K, m_dev, epi, part, m_min);
+    if (f.tile >= 0)
+      return f.splits > 1 ? launch_few_sum(f.splits, M, N, m_dev, epi, part, s) : hipSuccess;
     const W8Choice c = w8_choice(M, N, K, m_dev, epi.mode, part, m_min);
     if (!c.any_split) return hipSuccess;
     const int bn_out = epi.mode == EPI_SWIGLU ? kW8SplitBN / 2 : kW8SplitBN;

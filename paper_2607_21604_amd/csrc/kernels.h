@@ -106,6 +106,15 @@ hipError_t launch_gemm_fixup(const void *A, int lda, const void *B, int ldb, int
                              int K, const int32_t *m_dev, int dtype, const Epi &epi,
                              hipStream_t s, float *part = nullptr, int m_min = 0);
 size_t gemm_part_floats(int M, int N, int K, int mode);
+// ---- k_few.hip ----------------------------------------------------------------------
+// The few-row GEMM with tile `tile` of few_tile (k_gemm.hip picks it); splits > 1: RESID only,
+// partials to part [splits][M][N], added to the residual by launch_few_sum.
+constexpr int kFewMaxSplits = 8;
+hipError_t launch_few(int tile, int splits, const void *A, int lda, const void *B, int ldb, int M,
+                      int N, int K, const int32_t *m_dev, const Epi &e, float *part,
+                      hipStream_t s);
+hipError_t launch_few_sum(int splits, int M, int N, const int32_t *m_dev, const Epi &e,
+                          const float *part, hipStream_t s);
 int gemm_cu_count();
 
 // ---- k_attn.hip ---------------------------------------------------------------------

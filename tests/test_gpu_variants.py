@@ -1,5 +1,6 @@
 """Parity of the size- and alignment-dependent kernel variants at the edges of their ranges:
-the wide quantiser against the oracle at ties, the LM head over several rows, the fp32 tiles."""
+the wide quantiser against the oracle at ties, the LM head over several rows, the fp32 tiles,
+the few-row projections."""
 import numpy as np
 import pytest
 import torch
@@ -7,7 +8,7 @@ import torch
 import oracle
 import synthetic
 from paper_2607_21604_amd import akvs
-from tests.gpu_util import DEV, f64, max_rel, to_dev
+from tests.gpu_util import DEV, f64, max_rel, storage_round, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -156,3 +157,42 @@ def test_fp32_attention(hq, hkv, hd, rows, n_keys):
     ref = oracle.attention(q.astype(np.float64), pos, k.astype(np.float64), v.astype(np.float64),
                            np.arange(n_keys)).reshape(rows, -1)
     assert max_rel(f64(out), ref) < 1e-5
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,ffn,rows", [
+    (2048, 16, 4, 128, 2176, 1), (2048, 16, 4, 128, 2176, 31), (2048, 16, 4, 128, 2176, 33),
+    (2048, 16, 4, 128, 2176, 65), (2048, 16, 4, 128, 2176, 97), (2048, 16, 4, 128, 2176, 200),
+    (2048, 16, 4, 128, 2176, 385), (3072, 24, 8, 128, 8192, 129), (4096, 32, 4, 128, 8192, 96),
+    (320, 5, 1, 64, 448, 1), (320, 5, 1, 64, 448, 95), (320, 5, 1, 64, 448, 130),
+    (64, 1, 1, 64, 64, 40)])
+def test_few_row_projections(d, hq, hkv, hd, ffn, rows):
+    """The few-row tiles at row, column and K remainders (K of 2176 and 320 are odd multiples of
+    64 or 128), with and without the K split, against the oracle; the same bits twice."""
+    shape = synthetic.ModelShape("v", 1, d, hq, hkv, hd, ffn, 64, 1e4)
+    w = synthetic.make_weights(shape, seed=rows, embed=False)
+    dims = oracle.dims_from(shape)
+    m = akvs.model_cfg(shape)
+    lwd = {k: to_dev(t) for k, t in w["layers"][0].items()}
+    lws = akvs.layer_array({"layers": [lwd]})[0]
+    h = synthetic.random_array((rows, d), 6).astype(np.float32)
+    pos = np.arange(rows, dtype=np.int32) * 2
+    table = torch.empty((2 * rows, hd // 2, 2), device=DEV)
+    akvs.akvs_rope_table(2 * rows, hd, 1e4, table)
+    att = storage_round(synthetic.random_array((rows, hq * hd), 7), torch.bfloat16)
+    nbytes = akvs.akvs_step_workspace_size(m, rows)
+    runs = []
+    for fill in (0, 255):  # what the workspace holds does not matter
+        ws = torch.full((nbytes,), fill, dtype=torch.uint8, device=DEV)
+        q = torch.empty((rows, hq, hd), dtype=torch.bfloat16, device=DEV)
+        kf, vf = (torch.empty((rows, hkv, hd), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+        hdev = to_dev(h)
+        akvs.akvs_probe_qkv(hdev, rows, to_dev(pos), m, lws, table, 2 * rows, q, kf, vf, ws)
+        akvs.akvs_probe_out_mlp(hdev, rows, to_dev(att), m, lws, ws)
+        runs.append((q, kf, vf, hdev))
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
+    sw = oracle.split_layer(w["layers"][0], dims)
+    for got, ref in zip(runs[0], oracle.model.project_qkv(h.astype(np.float64), pos, sw, dims)):
+        assert max_rel(f64(got), ref) < 1e-2  # a bf16 rounding of inputs and outputs: 2^-8 each
+    ref = oracle.model.output_and_mlp(h.astype(np.float64), f64(att), sw, dims)
+    assert max_rel(f64(runs[0][3]), ref) < 1e-2
