@@ -473,8 +473,8 @@ akvs_status out_mlp(const akvs_model_cfg *m, const akvs_layer_w &w, float *h, in
 // Attention split plan of full_layer over n rows (into lb.plan, read by every such layer).
 hipError_t plan_full_layers(const akvs_model_cfg *m, int n, const LayerBufs &lb,
                             hipStream_t stream) {
-  return launch_attention_plan(nullptr, 0, n, nullptr, n, m->n_q_heads, m->head_dim, m->dtype,
-                               lb.part_rows, lb.plan, stream);
+  return launch_attention_plan(nullptr, 0, n, nullptr, n, m->n_q_heads, m->n_kv_heads, m->head_dim,
+                               m->dtype, lb.part_rows, lb.plan, stream);
 }
 
 // One ordinary causal layer over n consecutive rows at positions pos0.. (keys written to
@@ -926,8 +926,8 @@ akvs_status akvs_sparse_query_attention(const void *q, const int32_t *positions,
   }
   if (plan)
     LAUNCH(AKVS_K_OTHER, launch_attention_plan(positions, 0, n_rows, nullptr, n_keys,
-                                               m->n_q_heads, m->head_dim, m->dtype, part_rows,
-                                               plan, stream));
+                                               m->n_q_heads, m->n_kv_heads, m->head_dim, m->dtype,
+                                               part_rows, plan, stream));
   LAUNCH(AKVS_K_ATTENTION, launch_attention(q, positions, 0, n_rows, nullptr, k, v, n_keys,
                                             m->n_q_heads, m->n_kv_heads, m->head_dim, m->dtype,
                                             out, part_o, part_ml, part_rows, stream, nullptr,
@@ -1081,11 +1081,11 @@ akvs_status akvs_reuse_prefill(const int32_t *tokens, const void *embed, const a
   LAUNCH(AKVS_K_OTHER, launch_gather_rows(b.h_full, T, b.rows, cap, b.n_rows, D, b.h_probe,
                                           stream));
   // one key-split plan per row set, for every layer's attention over it
-  LAUNCH(AKVS_K_OTHER, launch_attention_plan(b.rows, 0, cap, b.n_rows, T, m->n_q_heads, hd,
+  LAUNCH(AKVS_K_OTHER, launch_attention_plan(b.rows, 0, cap, b.n_rows, T, m->n_q_heads, hkv, hd,
                                              m->dtype, b.lb.part_rows, b.plan_rows, stream));
   LAUNCH(AKVS_K_OTHER, launch_attention_plan(nullptr, Tc, cfg->query_len, nullptr, T,
-                                             m->n_q_heads, hd, m->dtype, b.lb.part_rows, b.plan_q,
-                                             stream));
+                                             m->n_q_heads, hkv, hd, m->dtype, b.lb.part_rows,
+                                             b.plan_q, stream));
   // from the check layer on: recomputed rows only, every unit token corrected
   const int qkvw = hqw + 2 * kvw;
   for (int l = c; l < L; ++l) {
@@ -1236,10 +1236,10 @@ akvs_status akvs_reuse_prefill_batch(const int32_t *const *tokens, int32_t batch
     LAUNCH(AKVS_K_OTHER, launch_copy_ints_at(b.req[i].rows, cap, b.n_rows + i, b.pos,
                                              b.row_off + i, stream));
     LAUNCH(AKVS_K_OTHER, launch_attention_plan(b.req[i].rows, 0, cap, b.n_rows + i,
-                                               (int)mt.t_all, m->n_q_heads, hd, m->dtype,
+                                               (int)mt.t_all, m->n_q_heads, hkv, hd, m->dtype,
                                                b.lb.part_rows, b.req[i].plan_rows, stream));
     LAUNCH(AKVS_K_OTHER, launch_attention_plan(nullptr, (int)mt.t_ctx, cfgs[i].query_len,
-                                               nullptr, (int)mt.t_all, m->n_q_heads, hd,
+                                               nullptr, (int)mt.t_all, m->n_q_heads, hkv, hd,
                                                m->dtype, b.lb.part_rows, b.req[i].plan_q,
                                                stream));
   }

@@ -26,27 +26,26 @@ namespace akvs {
 // (standalone timing, not in the repository). A 32-lane read phase touches 4 rows x 64
 // bytes, at 16-bank offsets: no conflicts.
 
-// Block shape: one query head per block, 32-row waves. With about 250 VGPRs a compute unit
-// holds eight waves, so blocks of 8 waves (one per unit) or 4 (two per unit) use every SIMD
-// evenly; the first four waves stage the K / V tiles.
+// Block shape: 32-row waves. With about 250 VGPRs a compute unit holds eight waves, so blocks
+// of 8 waves (one per unit) or 4 (two per unit) use every SIMD evenly; the first four waves
+// stage the K / V tiles.
 //  - 256 rows (8 waves sharing each K / V tile) when that still makes 512 blocks (32B probe
 //    layer, 5527 rows over 16128 keys: 1094 us against 1383 us for blocks that grouped the
 //    five query heads of a KV head over 32 rows, whose 5 waves leave SIMDs unevenly loaded);
 //  - else 128 rows (4 waves) per block; when those make fewer than 512 blocks the key range
 //    is split as well (see attn_splits). (32B probe layer at r = 1/10, 3050 rows: 664 us
 //    against 751 us for the five-head 32-row blocks; the 3B full prefill measured the same
-//    with three-head 64-row blocks. Grouped-head blocks never make more blocks than these,
-//    so they are not used; the kernel still takes the general head grouping gh.)
-struct AttnShape {
-  int gh, n_groups, nrb;
-};
-static inline AttnShape attn_shape(int G, int rows, int hkv) {
-  AttnShape a{0, 0, 0};
-  if (G < 1) return a;
-  a.gh = 1;
-  a.n_groups = G;
-  a.nrb = (long long)((rows + 255) / 256) * hkv * G >= 512 ? 8 : 4;
-  return a;
+//    with three-head 64-row blocks.)
+static inline int attn_waves(int rows, int hq) {
+  return (long long)((rows + 255) / 256) * hq >= 512 ? 8 : 4;
+}
+
+// Short contexts run whole: a piece of the key range costs about 1.6 us per 64 keys, a split
+// about 8 us more for its fixed part and the merge. Square calls (a full prefill) of 203, 384
+// and 768 keys took 14, 19 and 25 us split (plan not counted), 11, 15 and 22 us whole; 64
+// rows over 512 keys 12 us split, 18 us whole, hence the two bounds.
+static inline bool attn_whole(int rows, int n_keys) {
+  return n_keys <= 384 || (n_keys <= 768 && 2LL * rows >= n_keys);
 }
 
 // Planned split (launch_attention_plan, then launch_attention with the plan): for calls
@@ -66,31 +65,64 @@ static inline AttnShape attn_shape(int G, int rows, int hkv) {
 // layers at 1992 rows over 4516 keys the 128-row blocks took 101 us against 89 us for two
 // rounds of 256-row blocks, which is what sets the 3/4 bound (standalone harness, not in
 // the repository).
+// Few rows are also packed: the G query heads of a KV head over the same rows form one list
+// of G x rows (row, head) pairs, row by row, so that a tile's 32-row waves are full and a K / V
+// tile is read once for more of them. Taken where it leaves at least a tenth less padding,
+// and the tiles are many or long (else it only leaves fewer blocks: 64 rows over 1000 keys
+// 21 us packed, 18 us not). Up to 16 pieces per tile where few rows see many keys. Whole calls
+// with their plan, without both -> with: 3B heads over 16000 keys 9 / 64 / 159 / 400 rows
+// 51 / 65 / 70 / 87 -> 37 / 49 / 54 / 78 us, 32B heads 62 / 81 / 87 / 145 -> 38 / 52 / 61 / 101;
+// 400 rows over 2500 and 5000 keys, 3B 36 and 48 -> 33 and 41; 159 rows over 1000 keys 23 -> 21.
+// (16 pieces at 250 rows of the 32B heads, or under 2500 keys, cost 2 to 5 % more than 8.)
 struct AttnEqShape {
   int rb, budget, max_pc;
   bool use;
+  int pack;  // query heads listed together: 1, or G
 };
-constexpr int kAttnMaxPieces = 8;  // the merge's all-at-once path
-static inline AttnEqShape attn_eq_shape(int rows, int hq, int hd, int dtype, long long part_rows,
-                                        int cus) {
-  AttnEqShape e{0, 0, 0, false};
-  if (dtype != AKVS_BF16 || rows <= 0 || hq <= 0 || (hd != 64 && hd != 128)) return e;
-  const int p128 = 2 * cus / hq, p256 = cus / hq;
-  const int nt128 = (rows + 127) / 128, nt256 = (rows + 255) / 256;
+constexpr int kAttnMaxPieces = 8, kAttnFewPieces = 16;  // the merge's all-at-once path
+static inline int attn_max_pieces(int rows, int n_keys) {
+  return rows <= 192 && n_keys > 4096 ? kAttnFewPieces : kAttnMaxPieces;
+}
+
+// rb and budget for `rows` rows (or pairs) of `lists` row lists; false where the tiles fill
+// the chip or the plan's 64 tiles do not cover them.
+static inline bool attn_eq_blocks(long long rows, int lists, int cus, int *rb, int *budget) {
+  const int p128 = 2 * cus / lists, p256 = cus / lists;
+  const long long nt128 = (rows + 127) / 128, nt256 = (rows + 255) / 256;
   if (nt128 >= 3 && 4 * nt128 <= 3 * p128) {
-    e.rb = 128;
-    e.budget = p128;
+    *rb = 128;
+    *budget = p128;
   } else if (p256 >= 1 && 2 * nt256 <= p256) {
-    e.rb = 256;
-    e.budget = p256;
+    *rb = 256;
+    *budget = p256;
   } else if (p256 >= 1 && nt256 < 2 * p256) {
-    e.rb = 256;
-    e.budget = 2 * p256;
+    *rb = 256;
+    *budget = 2 * p256;
   } else {
-    return e;
+    return false;
   }
-  if ((rows + e.rb - 1) / e.rb > 64) return e;
-  e.max_pc = (int)std::min<long long>(kAttnMaxPieces, part_rows / rows);
+  return (rows + *rb - 1) / *rb <= 64;
+}
+
+static inline AttnEqShape attn_eq_shape(int rows, int hq, int hkv, int n_keys, int hd, int dtype,
+                                        long long part_rows, int cus) {
+  AttnEqShape e{0, 0, 0, false, 1};
+  if (dtype != AKVS_BF16 || rows <= 0 || hq <= 0 || (hd != 64 && hd != 128)) return e;
+  if (attn_whole(rows, n_keys)) return e;
+  if (!attn_eq_blocks(rows, hq, cus, &e.rb, &e.budget)) return e;
+  const int G = hq / hkv;
+  int rb, budget;
+  if (G > 1 && (rows > 128 || n_keys > 4096) &&
+      attn_eq_blocks((long long)rows * G, hkv, cus, &rb, &budget)) {
+    const long long single = (long long)((rows + e.rb - 1) / e.rb) * e.rb * hq;
+    const long long packed = ((long long)rows * G + rb - 1) / rb * rb * hkv;
+    if (10 * packed <= 9 * single) {
+      e.rb = rb;
+      e.budget = budget;
+      e.pack = G;
+    }
+  }
+  e.max_pc = (int)std::min<long long>(attn_max_pieces(rows, n_keys), part_rows / rows);
   e.use = e.max_pc >= 2;
   return e;
 }
@@ -104,15 +136,16 @@ static inline AttnEqShape attn_eq_shape(int rows, int hq, int hd, int dtype, lon
 __global__ __launch_bounds__(64) void k_attn_plan(const int32_t *pos, int pos0, int rows,
                                                   const int32_t *rows_dev,
                                                   const int32_t *row_base, int n_keys, int rb,
-                                                  int budget, int max_pc, int4 *plan) {
+                                                  int budget, int max_pc, int pack, int4 *plan) {
   const int lane = threadIdx.x;
   int R = rows;
   if (rows_dev) R = min(R, *rows_dev);
+  R *= pack;  // (row, head) pairs
   if (row_base && pos) pos += *row_base;
   const int nt = (R + rb - 1) / rb;
   int kt = 0;
   if (lane < nt) {
-    const int e = min((lane + 1) * rb, R) - 1;
+    const int e = (min((lane + 1) * rb, R) - 1) / pack;
     kt = (min(n_keys, (pos ? pos[e] : pos0 + e) + 1) + 63) >> 6;
   }
   int ktmax = kt;
@@ -141,8 +174,9 @@ __global__ __launch_bounds__(64) void k_attn_plan(const int32_t *pos, int pos0, 
   if (lane == 0) plan[0] = make_int4(nt, total, cmax, 0);
 }
 
-// A block serves head group hg of KV head kvh: 32 * nrb query rows x gh query heads. Wave
-// w owns 32 rows (row block w / gh) of query head kvh * G + hg * gh + w % gh. Waves 0-3
+// A block serves 32 * nrb rows of one query head (pack 1), or as many (row, head) pairs of the
+// G = pack query heads of KV head kvh: pair v is row v / G, head kvh * G + v % G. Wave w owns
+// 32 of them. Waves 0-3
 // stage each 64-key K / V tile in LDS for all of them (double buffered, the next tile in
 // flight during the current one: hd 128 straight from global memory into LDS, hd 64 through
 // registers). Block b serves KV head b % Hkv, so the blocks streaming one head's keys run on
@@ -153,7 +187,7 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
                                                    const int32_t *rows_dev,
                                                    const bf16_t *__restrict__ Kc,
                                                    const bf16_t *__restrict__ Vc, int n_keys,
-                                                   int hq, int hkv, int gh, int n_groups,
+                                                   int hq, int hkv, int pack,
                                                    int nrb, int n_tiles, int n_splits,
                                                    int split_keys,
                                                    float scale_log2,
@@ -190,11 +224,12 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
   const int G = hq / hkv;
   const int kvh = blockIdx.x % hkv;
   int rest = (int)(blockIdx.x / hkv);
-  const int hg = rest % n_groups;
-  rest /= n_groups;
-  const int head = kvh * G + hg * gh + wave % gh;
+  const int lists = pack > 1 ? 1 : G;  // row lists of a KV head
+  const int hg = rest % lists;
+  rest /= lists;
   int R = rows;
   if (rows_dev) R = min(R, *rows_dev);
+  R *= pack;
   const int rb_rows = 32 * nrb;
   int split, tile, n_part = n_splits, kv_begin = -1;
   if (plan) {  // item `rest` of the call's plan (see k_attn_plan)
@@ -216,8 +251,10 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
   const int row0 = tile * rb_rows;
   if (tile < 0 || row0 >= R) return;
   const int hi = lane >> 5;  // which half of a row's 32 keys (and 32 dims) this lane holds
-  const int r = row0 + (wave / gh) * 32 + (lane & 31);
-  const bool rvalid = r < R;
+  const int v = row0 + wave * 32 + (lane & 31);
+  const bool rvalid = v < R;
+  const int r = pack > 1 ? v / pack : v;
+  const int head = kvh * G + (pack > 1 ? v - r * pack : hg);
   const int rp = rvalid ? (pos ? pos[r] : pos0 + r) : -1;
   const int rpos = rvalid ? rp : 0;
   int wmax = rp, wmin = rvalid ? rp : 0x7fffffff;
@@ -246,7 +283,7 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
   // Q^T operand of S: lane holds dims ks*16 + hi*8 .. +7 of its row
   bf16x8_t qf[KS];
   {
-    const bf16_t *qrow = Q + ((size_t)(rvalid ? r : row0) * hq + head) * HD + hi * 8;
+    const bf16_t *qrow = Q + ((size_t)(rvalid ? r : row0 / pack) * hq + head) * HD + hi * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8_t *>(qrow + ks * 16);
     // vmcnt(0): the query fragments are complete before the key loop, so the loop's waits
@@ -649,9 +686,10 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
 // split a tile may use fewer splits than the launch's count: l = -1 after its last one
 // ends the list (the slots past it are stale); l = -1 in the first slot marks a row whose
 // tile ran as one piece and whose output the attention block wrote itself.
-// Thread = 8 consecutive head dims of one (row, head) (16-byte loads and stores). Up to 8
+// Thread = 8 consecutive head dims of one (row, head) (16-byte loads and stores). Up to MAXS
 // splits, all (m, l) pairs and partial outputs are requested at once; with more, the
 // maxima first, then the splits in order.
+template <int MAXS>
 __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__ part_o,
                                                       const float *__restrict__ part_ml,
                                                       int n_splits, int rows,
@@ -672,11 +710,11 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
   float mx = -INFINITY, l = 0.f, a[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) a[i] = 0.f;
-  if (n_splits <= 8) {  // every partial of this item requested at once
-    float2 ml[8];
-    float o[8][8];
+  if (n_splits <= MAXS) {  // every partial of this item requested at once
+    float2 ml[MAXS];
+    float o[MAXS][8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < MAXS; ++u) {
       if (u < n_splits) {
         const size_t pi = u * stride + item;
         ml[u] = *reinterpret_cast<const float2 *>(part_ml + 2 * pi);
@@ -685,15 +723,15 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
     }
     int n = n_splits;  // up to the first end mark
 #pragma unroll
-    for (int u = 7; u >= 0; --u)
+    for (int u = MAXS - 1; u >= 0; --u)
       if (u < n_splits && ml[u].y < 0.f) n = u;
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < MAXS; ++u)
       if (u < n) mx = fmaxf(mx, ml[u].x);
     if (n == 0) return;  // the attention wrote this row's output itself
     const float moff = mx == -INFINITY ? 0.f : mx;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < MAXS; ++u) {
       if (u >= n || ml[u].x == -INFINITY) continue;
       const float w = exp2f(ml[u].x - moff) * ml[u].y;
       l += w;
@@ -850,10 +888,9 @@ __global__ __launch_bounds__(512) void k_attn_f32(const float *__restrict__ Q, c
 }
 
 int attn_splits(int rows, int hq, int hkv, int n_keys) {
-  const AttnShape a = attn_shape(hq / hkv, rows, hkv);
-  if (a.gh == 0 || rows <= 0) return 1;
-  const int rb = 32 * a.nrb;
-  const long long base = (long long)((rows + rb - 1) / rb) * hkv * a.n_groups;
+  if (hq < hkv || rows <= 0 || attn_whole(rows, n_keys)) return 1;
+  const int rb = 32 * attn_waves(rows, hq);
+  const long long base = (long long)((rows + rb - 1) / rb) * hq;
   if (base >= 512) return 1;                        // two blocks per compute unit already
   long long sp = (768 + base - 1) / base;           // else aim at ~768 blocks (measured)
   const long long cap = (n_keys + 255) / 256;        // at least 256 keys per split
@@ -869,18 +906,21 @@ int attn_split_keys(int n_keys, int n_splits) {
 
 int attn_part_splits(int rows, int hq, int hkv, int hd, int n_keys) {
   const int sp = attn_splits(rows, hq, hkv, n_keys);
-  const AttnEqShape e =
-      attn_eq_shape(rows, hq, hd, AKVS_BF16, (long long)kAttnMaxPieces * rows, gemm_cu_count());
-  return e.use ? std::max(sp, kAttnMaxPieces) : sp;
+  const int most = attn_max_pieces(rows, n_keys);
+  const AttnEqShape e = attn_eq_shape(rows, hq, hkv, n_keys, hd, AKVS_BF16,
+                                      (long long)most * rows, gemm_cu_count());
+  return e.use ? std::max(sp, most) : sp;
 }
 
 hipError_t launch_attention_plan(const int32_t *pos, int pos0, int rows, const int32_t *rows_dev,
-                                 int n_keys, int hq, int hd, int dtype, long long part_rows,
-                                 int32_t *plan, hipStream_t s, const int32_t *row_base) {
-  const AttnEqShape e = attn_eq_shape(rows, hq, hd, dtype, part_rows, gemm_cu_count());
+                                 int n_keys, int hq, int hkv, int hd, int dtype,
+                                 long long part_rows, int32_t *plan, hipStream_t s,
+                                 const int32_t *row_base) {
+  const AttnEqShape e =
+      attn_eq_shape(rows, hq, hkv, n_keys, hd, dtype, part_rows, gemm_cu_count());
   if (!e.use || !plan) return hipSuccess;  // launch_attention will not read it either
   hipLaunchKernelGGL(k_attn_plan, dim3(1), dim3(64), 0, s, pos, pos0, rows, rows_dev, row_base,
-                     n_keys, e.rb, e.budget, e.max_pc, reinterpret_cast<int4 *>(plan));
+                     n_keys, e.rb, e.budget, e.max_pc, e.pack, reinterpret_cast<int4 *>(plan));
   return hipGetLastError();
 }
 
@@ -896,56 +936,49 @@ hipError_t launch_attention(const void *q, const int32_t *pos, int pos0, int row
     const bf16_t *K = reinterpret_cast<const bf16_t *>(k);
     const bf16_t *V = reinterpret_cast<const bf16_t *>(v);
     bf16_t *O = reinterpret_cast<bf16_t *>(out);
-    AttnShape a = attn_shape(hq / hkv, rows, hkv);
-    if (a.gh == 0) return hipErrorInvalidValue;
-    const AttnEqShape e = attn_eq_shape(rows, hq, hd, dtype, part_rows, gemm_cu_count());
-    if (plan && part_o && part_ml && e.use) {  // the split that launch_attention_plan planned
-      const int nrb = e.rb / 32;
-      const int items = std::max((rows + e.rb - 1) / e.rb, e.budget);
-      dim3 g(items * hq), b(64 * nrb);
-      const int4 *P = reinterpret_cast<const int4 *>(plan);
-#define AKVS_ATTN_PLANNED(HD_, PREF_)                                                             \
-  hipLaunchKernelGGL((k_attn_bf16<HD_, PREF_>), g, b, 0, s, Q, pos, pos0, rows, rows_dev, K, V,     \
-                     n_keys, hq, hkv, 1, hq / hkv, nrb, 1, e.max_pc, 0, scale_log2, O,             \
-                     reinterpret_cast<bf16_t *>(part_o), part_ml, row_base, P)
-      if (hd == 128) {
-        AKVS_ATTN_PLANNED(128, false);
-      } else {
-        if (nrb == 4) AKVS_ATTN_PLANNED(64, true); else AKVS_ATTN_PLANNED(64, false);
-      }
-#undef AKVS_ATTN_PLANNED
-      hipError_t er = hipGetLastError();
-      if (er != hipSuccess) return er;
-      const long long threads = (long long)rows * hq * (hd / 8);
-      hipLaunchKernelGGL(k_attn_combine, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
-                         reinterpret_cast<const bf16_t *>(part_o), part_ml, e.max_pc, rows,
-                         rows_dev, hq, hd, O, row_base, P);
-      return hipGetLastError();
+    if (hq < hkv) return hipErrorInvalidValue;
+    const AttnEqShape e =
+        attn_eq_shape(rows, hq, hkv, n_keys, hd, dtype, part_rows, gemm_cu_count());
+    const bool planned = plan && part_o && part_ml && e.use;  // as launch_attention_plan did
+    int nrb, n_splits, split_keys = 0, n_tiles = 1, pack = 1, blocks;
+    if (planned) {
+      nrb = e.rb / 32;
+      pack = e.pack;
+      n_splits = e.max_pc;
+      const long long n = ((long long)rows * pack + e.rb - 1) / e.rb;
+      blocks = (int)std::max<long long>(n, e.budget) * (pack > 1 ? hkv : hq);
+    } else {
+      nrb = attn_waves(rows, hq);
+      n_splits = part_o && part_ml ? attn_splits(rows, hq, hkv, n_keys) : 1;
+      if ((long long)n_splits * rows > part_rows)
+        n_splits = (int)std::max(1LL, part_rows / rows);
+      split_keys = attn_split_keys(n_keys, n_splits);
+      n_tiles = (rows + 32 * nrb - 1) / (32 * nrb);
+      blocks = n_tiles * hq * n_splits;
     }
-    int n_splits = part_o && part_ml ? attn_splits(rows, hq, hkv, n_keys) : 1;
-    if ((long long)n_splits * rows > part_rows) n_splits = (int)std::max(1LL, part_rows / rows);
-    const int split_keys = attn_split_keys(n_keys, n_splits);
-    const int n_tiles = (rows + 32 * a.nrb - 1) / (32 * a.nrb);
-    dim3 g(n_tiles * hkv * a.n_groups * n_splits), b(64 * a.nrb * a.gh);
-    const bool pref = a.nrb * a.gh <= 4;  // hd 64 (see PREF in the kernel)
+    const dim3 g(blocks), b(64 * nrb);
+    const int4 *P = planned ? reinterpret_cast<const int4 *>(plan) : nullptr;
 #define AKVS_ATTN(HD_, PREF_)                                                                    \
   hipLaunchKernelGGL((k_attn_bf16<HD_, PREF_>), g, b, 0, s, Q, pos, pos0, rows, rows_dev, K, V,    \
-                     n_keys, hq, hkv, a.gh, a.n_groups, a.nrb, n_tiles, n_splits, split_keys,      \
-                     scale_log2, O, reinterpret_cast<bf16_t *>(part_o), part_ml, row_base,         \
-                     nullptr)
+                     n_keys, hq, hkv, pack, nrb, n_tiles, n_splits, split_keys, scale_log2, O,     \
+                     reinterpret_cast<bf16_t *>(part_o), part_ml, row_base, P)
     if (hd == 128) {
       AKVS_ATTN(128, false);  // the direct-to-LDS staging, 4- and 8-wave blocks alike
     } else {
-      if (pref) AKVS_ATTN(64, true); else AKVS_ATTN(64, false);
+      if (nrb == 4) AKVS_ATTN(64, true); else AKVS_ATTN(64, false);  // (see PREF in the kernel)
     }
 #undef AKVS_ATTN
     if (n_splits > 1) {
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      const long long threads = (long long)rows * hq * (hd / 8);
-      hipLaunchKernelGGL(k_attn_combine, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
-                         reinterpret_cast<const bf16_t *>(part_o), part_ml, n_splits, rows,
-                         rows_dev, hq, hd, O, row_base, nullptr);
+      hipError_t er = hipGetLastError();
+      if (er != hipSuccess) return er;
+      const dim3 gc((unsigned)(((long long)rows * hq * (hd / 8) + 255) / 256)), bc(256);
+      const bf16_t *po = reinterpret_cast<const bf16_t *>(part_o);
+      if (n_splits <= 8)
+        hipLaunchKernelGGL((k_attn_combine<8>), gc, bc, 0, s, po, part_ml, n_splits, rows, rows_dev,
+                           hq, hd, O, row_base, P);
+      else
+        hipLaunchKernelGGL((k_attn_combine<16>), gc, bc, 0, s, po, part_ml, n_splits, rows,
+                           rows_dev, hq, hd, O, row_base, P);
     }
   } else {
     const float scale = 1.4426950408889634f / sqrtf((float)hd);

@@ -136,8 +136,9 @@ hipError_t launch_attention(const void *q, const int32_t *pos, int pos0, int row
 // plan serves every layer over the same rows.
 constexpr int kAttnPlanInts = 4 * 65;
 hipError_t launch_attention_plan(const int32_t *pos, int pos0, int rows, const int32_t *rows_dev,
-                                 int n_keys, int hq, int hd, int dtype, long long part_rows,
-                                 int32_t *plan, hipStream_t s, const int32_t *row_base = nullptr);
+                                 int n_keys, int hq, int hkv, int hd, int dtype,
+                                 long long part_rows, int32_t *plan, hipStream_t s,
+                                 const int32_t *row_base = nullptr);
 // number of key splits launch_attention uses for `rows` rows over n_keys keys
 int attn_splits(int rows, int hq, int hkv, int n_keys);
 // partial slots per row that the part_o / part_ml buffers of such a call should hold

@@ -1,6 +1,6 @@
 """Parity of the size- and alignment-dependent kernel variants at the edges of their ranges:
 the wide quantiser against the oracle at ties, the LM head over several rows, the fp32 tiles,
-the few-row projections."""
+the few-row projections, the attention over packed head lists and short contexts."""
 import numpy as np
 import pytest
 import torch
@@ -196,3 +196,30 @@ def test_few_row_projections(d, hq, hkv, hd, ffn, rows):
         assert max_rel(f64(got), ref) < 1e-2  # a bf16 rounding of inputs and outputs: 2^-8 each
     ref = oracle.model.output_and_mlp(h.astype(np.float64), f64(att), sw, dims)
     assert max_rel(f64(runs[0][3]), ref) < 1e-2
+
+
+@pytest.mark.parametrize("hq,hkv,hd,rows,n_keys", [
+    (10, 2, 128, 33, 4500), (14, 2, 128, 57, 5261), (40, 8, 128, 159, 1100), (3, 1, 64, 9, 4900),
+    (24, 8, 128, 1, 4300), (10, 2, 64, 200, 1700), (10, 2, 64, 192, 4097), (16, 1, 128, 193, 4100),
+    (16, 1, 128, 129, 1024), (14, 2, 128, 128, 1000),
+    (4, 2, 128, 203, 203), (4, 2, 64, 384, 768), (4, 2, 128, 385, 769), (4, 4, 128, 20, 384),
+    (4, 4, 128, 20, 385)])
+def test_attention_packed_heads_and_short_contexts(hq, hkv, hd, rows, n_keys):
+    """Row lists of several query heads (G of 3 to 16), up to 16 pieces per tile, and the key
+    counts around which short contexts run whole; the same result for any workspace content."""
+    rng = np.random.default_rng(rows)
+    pos = np.sort(rng.choice(n_keys, size=rows, replace=False)).astype(np.int32)
+    q, k, v = (storage_round(synthetic.random_array((n, h, hd), 50 + i), torch.bfloat16)
+               for i, (n, h) in enumerate([(rows, hq), (n_keys, hkv), (n_keys, hkv)]))
+    m = akvs.ModelCfg(1, 64, hq, hkv, hd, 64, 16, 1e4, 1e-6, akvs.AKVS_BF16)
+    ref = oracle.attention(f64(q), pos, f64(k), f64(v), np.arange(n_keys)).reshape(rows, -1)
+    nbytes = akvs.akvs_attention_workspace_size(m, rows, n_keys)
+    outs = []
+    for ws in (None, torch.full((max(nbytes, 1),), 255, dtype=torch.uint8, device=DEV),
+               torch.zeros(max(nbytes, 1), dtype=torch.uint8, device=DEV)):
+        out = torch.empty((rows, hq * hd), dtype=torch.bfloat16, device=DEV)
+        akvs.akvs_sparse_query_attention(to_dev(q), to_dev(pos), rows, to_dev(k), to_dev(v), n_keys,
+                                         m, out, ws)
+        assert max_rel(f64(out), ref) < 1e-2
+        outs.append(out)
+    assert torch.equal(outs[1], outs[2])
