@@ -156,7 +156,14 @@ def ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
+# The current stream's handle without building a torch.cuda.Stream object for it (3.1 us a
+# call, of the 9 us of a step entry's wrapper; 0.3 us this way), where this torch has it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def stream_handle(stream=None):
+    if stream is None and _raw_stream is not None:
+        return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
     s = stream if stream is not None else torch.cuda.current_stream()
     return ctypes.c_void_p(s.cuda_stream)
 
