@@ -401,6 +401,20 @@ __device__ __forceinline__ int find_chunk(const int4 *meta, int n_chunks, int t)
   return lo;
 }
 
+// find_chunk for a position that is the same in every lane of the wave: 64 starts per load, and
+// one load in all for up to 64 units, in place of a chain of log2(n) dependent ones (40 units
+// at 7B width from a 4-bit cache: 9.7 -> 8.9 us).
+__device__ __forceinline__ int find_chunk_wave(const int4 *meta, int n_chunks, int t) {
+  const int lane = threadIdx.x & 63;
+  int below = 0;  // units that start at or before t (starts ascend)
+  for (int i = 0; i < n_chunks; i += 64) {
+    const int n = __popcll(__ballot(meta[min(i + lane, n_chunks - 1)].x <= t && i + lane < n_chunks));
+    below += n;
+    if (n < 64) break;
+  }
+  return max(below - 1, 0);
+}
+
 // Per position: source flags, unit and rotation offset (query rows: fresh, no unit).
 struct CorrTok {
   int chunk, delta, fr;
@@ -596,7 +610,9 @@ __global__ __launch_bounds__(256) void k_correction_bf(CacheLayer cache, const f
       chunk = tok_chunk[t];
       delta = tok_delta[t];
     } else if (meta) {
-      chunk = find_chunk(meta, n_chunks, t);
+      // whole waves per position (all of the wave's lanes are here then): search together
+      chunk = (2 * side_units) % 64 == 0 ? find_chunk_wave(meta, n_chunks, t)
+                                         : find_chunk(meta, n_chunks, t);
       delta = meta[chunk].x;
     } else {
       delta = tok_delta[t];

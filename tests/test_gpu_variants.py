@@ -1,6 +1,7 @@
 """Parity of the size- and alignment-dependent kernel variants at the edges of their ranges:
 the wide quantiser against the oracle at ties, the LM head over several rows, the fp32 tiles,
-the few-row projections, the attention over packed head lists and short contexts."""
+the few-row projections, the attention over packed head lists and short contexts, the
+correction's unit search."""
 import numpy as np
 import pytest
 import torch
@@ -8,6 +9,8 @@ import torch
 import oracle
 import synthetic
 from paper_2607_21604_amd import akvs
+from tests.test_gpu_steps import (gpu_offset_and_correction, make_offset_case,
+                                  oracle_offset_and_correction)
 from tests.gpu_util import DEV, f64, max_rel, storage_round, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -223,3 +226,15 @@ def test_attention_packed_heads_and_short_contexts(hq, hkv, hd, rows, n_keys):
         assert max_rel(f64(out), ref) < 1e-2
         outs.append(out)
     assert torch.equal(outs[1], outs[2])
+
+
+@pytest.mark.parametrize("dtype,hkv,hd", [("bf16", 8, 128), ("bf16", 4, 128), ("bf16", 3, 64)])
+@pytest.mark.parametrize("units", [1, 63, 64, 65, 130])
+def test_correction_finds_the_unit_of_many(dtype, hkv, hd, units):
+    """A token's unit from the unit table alone, around multiples of the 64 starts that a wave
+    compares at once (whole waves per position at 1024 and 512 wide rows, not at 192)."""
+    lens = [1 + (5 * i) % 4 for i in range(units)]
+    cs = make_offset_case(dtype, lens, hkv, hd, seed=units)
+    mu_k, mu_v, k_corr, v_corr = gpu_offset_and_correction(cs, hkv, hd)
+    _, _, rk, rv = oracle_offset_and_correction(cs)
+    assert max_rel(f64(k_corr), rk) < 4e-3 and max_rel(f64(v_corr), rv) < 4e-3  # one bf16 rounding
