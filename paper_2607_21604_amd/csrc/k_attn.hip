@@ -768,11 +768,11 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
 // fp32 path (small models), on v_mfma_f32_16x16x4_f32. Block = 16 rows of one query head, 8
 // waves that take the 16-key tiles in turn (wave w the tiles w, w + 8, ...), each with its own
 // running maximum, sum and output, merged through LDS in wave order at the end: short calls
-// are bound by dependent memory round trips, so a tile needs two (K and V together) and no
-// barrier. Scores are formed transposed, S^T = K Q^T: lane l holds the scores of row l % 16
+// are bound by dependent memory round trips, so a tile needs one (K and V together, requested
+// a tile ahead) and no barrier. Scores are formed transposed, S^T = K Q^T: lane l holds the scores of row l % 16
 // at keys 4 (l / 16) + 0..3 of the tile, which is the operand layout of O^T = V^T P^T as it is.
 // 288 rows over 288 keys, 4 heads of 64: 30 us with one wave per (row, head) reading key rows
-// a lane each, 17 us here.
+// a lane each, 17 us here without the tile ahead, 9 us with it.
 template <int HD>
 __global__ __launch_bounds__(512) void k_attn_f32(const float *__restrict__ Q, const int32_t *pos,
                                                   int pos0, int rows, const int32_t *rows_dev,
@@ -815,26 +815,32 @@ __global__ __launch_bounds__(512) void k_attn_f32(const float *__restrict__ Q, c
 #pragma unroll
   for (int c = 0; c < C; ++c) o[c] = zero;
   float m = -INFINITY, l = 0.f;  // of row lr (l: this lane's quarter of the keys)
-  for (int key0 = wave * 16; key0 <= last; key0 += NW * 16) {
-    f32x4_t kf[C];
-    float vf[C][4];
-    {  // keys past the block's last one re-read it (masked below)
-      const float *k = Kc + ((size_t)min(key0 + lr, last) * hkv + kvh) * HD + lg * 4;
+  struct Tile {
+    f32x4_t k[C];
+    float v[C][4];
+  };
+  // keys past the block's last one re-read it (masked below)
+  auto fetch = [&](Tile &t, int key0) __attribute__((always_inline)) {
+    const float *k = Kc + ((size_t)min(key0 + lr, last) * hkv + kvh) * HD + lg * 4;
 #pragma unroll
-      for (int c = 0; c < C; ++c) kf[c] = *reinterpret_cast<const f32x4_t *>(k + 16 * c);
+    for (int c = 0; c < C; ++c) t.k[c] = *reinterpret_cast<const f32x4_t *>(k + 16 * c);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float *v = Vc + ((size_t)min(key0 + lg * 4 + e, last) * hkv + kvh) * HD + lr;
+    for (int e = 0; e < 4; ++e) {
+      const float *v = Vc + ((size_t)min(key0 + lg * 4 + e, last) * hkv + kvh) * HD + lr;
 #pragma unroll
-        for (int c = 0; c < C; ++c) vf[c][e] = v[16 * c];
-      }
+      for (int c = 0; c < C; ++c) t.v[c][e] = v[16 * c];
     }
-    f32x4_t s = zero;
+  };
+  auto attend = [&](const Tile &t, int key0) __attribute__((always_inline)) {
+    f32x4_t s0 = zero, s1 = zero;  // two chains of dependent MFMAs
 #pragma unroll
     for (int c = 0; c < C; ++c)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[c][e], s, 0, 0, 0);
+      for (int e = 0; e < 4; e += 2) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[c][e], qf[c][e], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[c][e + 1], qf[c][e + 1], s1, 0, 0, 0);
+      }
+    f32x4_t s = s0 + s1;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       s[e] = key0 + lg * 4 + e <= lim ? s[e] * scale_log2 : -INFINITY;
@@ -850,12 +856,25 @@ __global__ __launch_bounds__(512) void k_attn_f32(const float *__restrict__ Q, c
     l = l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
     m = m_new;
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      o[c] *= alpha;
+    for (int c = 0; c < C; ++c) o[c] *= alpha;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][e], p[e], o[c], 0, 0, 0);
-    }
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+        o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.v[c][e], p[e], o[c], 0, 0, 0);
+  };
+  constexpr int STEP = NW * 16;
+  Tile t0, t1;
+  int key0 = wave * 16;
+  if (key0 <= last) fetch(t0, key0);
+  while (key0 <= last) {  // the next tile's loads are in flight while this one is used
+    if (key0 + STEP <= last) fetch(t1, key0 + STEP);
+    attend(t0, key0);
+    key0 += STEP;
+    if (key0 > last) break;
+    if (key0 + STEP <= last) fetch(t0, key0 + STEP);
+    attend(t1, key0);
+    key0 += STEP;
   }
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
