@@ -451,6 +451,34 @@ Epi simple_epi(int mode, void *out, int ldo, int dtype) {
   return e;
 }
 
+// Embedding rows of n tokens, and the rotary table of n_pos positions from p0 (0: none).
+Setup setup_of(const akvs_model_cfg *m, const int32_t *tok, int n, const void *embed, float *h,
+               int p0, int n_pos, float *rope) {
+  Setup a{};
+  a.tok = tok;
+  a.n = n;
+  a.embed = embed;
+  a.vocab = m->vocab;
+  a.D = m->d_model;
+  a.h = h;
+  a.p0 = p0;
+  a.n_pos = n_pos;
+  a.hd = m->head_dim;
+  a.theta = (double)m->rope_theta;
+  a.rope = rope;
+  return a;
+}
+
+// ... and the tables of the unit tokens.
+Setup setup_units(Setup a, const int32_t *meta, int n_chunks, int32_t *tok_delta,
+                  int32_t *tok_chunk) {
+  a.meta = meta;
+  a.n_chunks = n_chunks;
+  a.tok_delta = tok_delta;
+  a.tok_chunk = tok_chunk;
+  return a;
+}
+
 // Attention output projection + MLP over rows (h updated in place).
 akvs_status out_mlp(const akvs_model_cfg *m, const akvs_layer_w &w, float *h, int rows,
                     const int32_t *rows_dev, const void *att, void *x, void *act, float *gpart,
@@ -473,8 +501,9 @@ akvs_status out_mlp(const akvs_model_cfg *m, const akvs_layer_w &w, float *h, in
 // Attention split plan of full_layer over n rows (into lb.plan, read by every such layer).
 hipError_t plan_full_layers(const akvs_model_cfg *m, int n, const LayerBufs &lb,
                             hipStream_t stream) {
-  return launch_attention_plan(nullptr, 0, n, nullptr, n, m->n_q_heads, m->n_kv_heads, m->head_dim,
-                               m->dtype, lb.part_rows, lb.plan, stream);
+  const AttnPlanReq r{nullptr, 0, n, nullptr, nullptr, lb.plan};
+  return launch_attention_plan(&r, 1, n, m->n_q_heads, m->n_kv_heads, m->head_dim, m->dtype,
+                               lb.part_rows, stream);
 }
 
 // One ordinary causal layer over n consecutive rows at positions pos0.. (keys written to
@@ -924,10 +953,11 @@ akvs_status akvs_sparse_query_attention(const void *q, const int32_t *positions,
       part_rows = (long long)(ml / ((size_t)m->n_q_heads * 2));
     }
   }
-  if (plan)
-    LAUNCH(AKVS_K_OTHER, launch_attention_plan(positions, 0, n_rows, nullptr, n_keys,
-                                               m->n_q_heads, m->n_kv_heads, m->head_dim, m->dtype,
-                                               part_rows, plan, stream));
+  if (plan) {
+    const AttnPlanReq r{positions, 0, n_rows, nullptr, nullptr, plan};
+    LAUNCH(AKVS_K_OTHER, launch_attention_plan(&r, 1, n_keys, m->n_q_heads, m->n_kv_heads,
+                                               m->head_dim, m->dtype, part_rows, stream));
+  }
   LAUNCH(AKVS_K_ATTENTION, launch_attention(q, positions, 0, n_rows, nullptr, k, v, n_keys,
                                             m->n_q_heads, m->n_kv_heads, m->head_dim, m->dtype,
                                             out, part_o, part_ml, part_rows, stream, nullptr,
@@ -989,9 +1019,8 @@ akvs_status akvs_full_prefill(const int32_t *tokens, int32_t n_tokens, int32_t p
   carve_full(ws, m, n_tokens, b);
   const int D = m->d_model;
   const size_t kvl = (size_t)n_tokens * m->n_kv_heads * m->head_dim * es_of(m->dtype);
-  LAUNCH(AKVS_K_OTHER, launch_rope_table(pos0, n_tokens, m->head_dim, (double)m->rope_theta,
-                                         b.rope, stream));
-  LAUNCH(AKVS_K_OTHER, launch_embed(tokens, n_tokens, embed, m->dtype, m->vocab, D, b.h, stream));
+  LAUNCH(AKVS_K_OTHER, launch_setup(setup_of(m, tokens, n_tokens, embed, b.h, pos0, n_tokens,
+                                             b.rope), m->dtype, stream));
   LAUNCH(AKVS_K_OTHER, plan_full_layers(m, n_tokens, b.lb, stream));
   for (int l = 0; l < m->n_layers; ++l) {
     st = full_layer(m, lw[l], b.h, n_tokens, pos0, b.rope, b.lb,
@@ -1051,9 +1080,9 @@ akvs_status akvs_reuse_prefill(const int32_t *tokens, const void *embed, const a
   char *v_corr = reinterpret_cast<char *>(out->v_corr);
 
   LAUNCH(AKVS_K_OTHER, put_ints(mt.m.data(), mt.m.size(), b.meta, stream));
-  LAUNCH(AKVS_K_OTHER, launch_rope_table(0, T, hd, (double)m->rope_theta, b.rope, stream));
-  LAUNCH(AKVS_K_OTHER, launch_token_setup(b.meta, nch, b.tok_delta, b.tok_chunk, stream));
-  LAUNCH(AKVS_K_OTHER, launch_embed(tokens, T, embed, m->dtype, m->vocab, D, b.h_full, stream));
+  LAUNCH(AKVS_K_OTHER,
+         launch_setup(setup_units(setup_of(m, tokens, T, embed, b.h_full, 0, T, b.rope), b.meta,
+                                  nch, b.tok_delta, b.tok_chunk), m->dtype, stream));
 
   // layers before the check layer: every token
   if (c > 0) LAUNCH(AKVS_K_OTHER, plan_full_layers(m, T, b.lb, stream));
@@ -1081,11 +1110,12 @@ akvs_status akvs_reuse_prefill(const int32_t *tokens, const void *embed, const a
   LAUNCH(AKVS_K_OTHER, launch_gather_rows(b.h_full, T, b.rows, cap, b.n_rows, D, b.h_probe,
                                           stream));
   // one key-split plan per row set, for every layer's attention over it
-  LAUNCH(AKVS_K_OTHER, launch_attention_plan(b.rows, 0, cap, b.n_rows, T, m->n_q_heads, hkv, hd,
-                                             m->dtype, b.lb.part_rows, b.plan_rows, stream));
-  LAUNCH(AKVS_K_OTHER, launch_attention_plan(nullptr, Tc, cfg->query_len, nullptr, T,
-                                             m->n_q_heads, hkv, hd, m->dtype, b.lb.part_rows,
-                                             b.plan_q, stream));
+  {
+    const AttnPlanReq r[2] = {{b.rows, 0, cap, b.n_rows, nullptr, b.plan_rows},
+                              {nullptr, Tc, cfg->query_len, nullptr, nullptr, b.plan_q}};
+    LAUNCH(AKVS_K_OTHER, launch_attention_plan(r, 2, T, m->n_q_heads, hkv, hd, m->dtype,
+                                               b.lb.part_rows, stream));
+  }
   // from the check layer on: recomputed rows only, every unit token corrected
   const int qkvw = hqw + 2 * kvw;
   for (int l = c; l < L; ++l) {
@@ -1117,9 +1147,8 @@ akvs_status akvs_reuse_prefill(const int32_t *tokens, const void *embed, const a
     // last layer: only the query rows' attention and MLP reach the returned outputs (the
     // recomputed unit rows only had to supply this layer's fresh keys and values)
     const int q = cfg->query_len;
-    LAUNCH(AKVS_K_OTHER, launch_copy_tail_rows(b.lb.q, (size_t)hqw * es, q, b.n_rows, b.q_last,
-                                               stream));
-    LAUNCH(AKVS_K_OTHER, launch_copy_tail_rows(b.h_probe, (size_t)D * 4, q, b.n_rows, b.h_last,
+    LAUNCH(AKVS_K_OTHER, launch_copy_tail_rows({b.lb.q, (size_t)hqw * es, b.q_last},
+                                               {b.h_probe, (size_t)D * 4, b.h_last}, q, b.n_rows,
                                                stream));
     LAUNCH(AKVS_K_ATTENTION, launch_attention(b.q_last, nullptr, Tc, q, nullptr, kl, vl, T,
                                               m->n_q_heads, hkv, hd, m->dtype, b.lb.att,
@@ -1202,8 +1231,9 @@ akvs_status akvs_reuse_prefill_batch(const int32_t *const *tokens, int32_t batch
     char *k_corr = reinterpret_cast<char *>(outs[i].k_corr);
     char *v_corr = reinterpret_cast<char *>(outs[i].v_corr);
     LAUNCH(AKVS_K_OTHER, put_ints(mt.m.data(), mt.m.size(), r.meta, stream));
-    LAUNCH(AKVS_K_OTHER, launch_token_setup(r.meta, nch, r.tok_delta, r.tok_chunk, stream));
-    LAUNCH(AKVS_K_OTHER, launch_embed(tokens[i], T, embed, m->dtype, m->vocab, D, r.h_full, stream));
+    LAUNCH(AKVS_K_OTHER,
+           launch_setup(setup_units(setup_of(m, tokens[i], T, embed, r.h_full, 0, 0, nullptr),
+                                    r.meta, nch, r.tok_delta, r.tok_chunk), m->dtype, stream));
     for (int l = 0; l < c; ++l) {
       if (l == 0) LAUNCH(AKVS_K_OTHER, plan_full_layers(m, T, b.lb_full, stream));
       st = full_layer(m, lw[l], r.h_full, T, 0, b.rope, b.lb_full, k_corr + l * corr_layer,
@@ -1235,13 +1265,11 @@ akvs_status akvs_reuse_prefill_batch(const int32_t *const *tokens, int32_t batch
                                             b.n_rows + i, D, b.h_probe, stream, b.row_off + i));
     LAUNCH(AKVS_K_OTHER, launch_copy_ints_at(b.req[i].rows, cap, b.n_rows + i, b.pos,
                                              b.row_off + i, stream));
-    LAUNCH(AKVS_K_OTHER, launch_attention_plan(b.req[i].rows, 0, cap, b.n_rows + i,
-                                               (int)mt.t_all, m->n_q_heads, hkv, hd, m->dtype,
-                                               b.lb.part_rows, b.req[i].plan_rows, stream));
-    LAUNCH(AKVS_K_OTHER, launch_attention_plan(nullptr, (int)mt.t_ctx, cfgs[i].query_len,
-                                               nullptr, (int)mt.t_all, m->n_q_heads, hkv, hd,
-                                               m->dtype, b.lb.part_rows, b.req[i].plan_q,
-                                               stream));
+    const AttnPlanReq pr[2] = {
+        {b.req[i].rows, 0, cap, b.n_rows + i, nullptr, b.req[i].plan_rows},
+        {nullptr, (int)mt.t_ctx, cfgs[i].query_len, nullptr, nullptr, b.req[i].plan_q}};
+    LAUNCH(AKVS_K_OTHER, launch_attention_plan(pr, 2, (int)mt.t_all, m->n_q_heads, hkv, hd,
+                                               m->dtype, b.lb.part_rows, stream));
   }
   for (int l = c; l < L; ++l) {
     LAUNCH(AKVS_K_NORM, launch_rmsnorm(b.h_probe, D, cap_sum, M_dev, nullptr, lw[l].attn_norm,
@@ -1278,11 +1306,10 @@ akvs_status akvs_reuse_prefill_batch(const int32_t *const *tokens, int32_t batch
       // last layer: only the query rows (the last q of each request's rows) go on
       const int q = cf.query_len;
       char *ql = reinterpret_cast<char *>(b.q_last) + (size_t)q_off * hqw * es;
-      LAUNCH(AKVS_K_OTHER, launch_copy_tail_rows(b.lb.q, (size_t)hqw * es, q, b.n_rows + i, ql,
-                                                 stream, b.row_off + i));
-      LAUNCH(AKVS_K_OTHER, launch_copy_tail_rows(b.h_probe, (size_t)D * 4, q, b.n_rows + i,
-                                                 b.h_last + (size_t)q_off * D, stream,
-                                                 b.row_off + i));
+      LAUNCH(AKVS_K_OTHER,
+             launch_copy_tail_rows({b.lb.q, (size_t)hqw * es, ql},
+                                   {b.h_probe, (size_t)D * 4, b.h_last + (size_t)q_off * D}, q,
+                                   b.n_rows + i, stream, b.row_off + i));
       LAUNCH(AKVS_K_ATTENTION,
              launch_attention(ql, nullptr, Tc, q, nullptr, kl, vl, T, m->n_q_heads, hkv, hd,
                               m->dtype, reinterpret_cast<char *>(b.lb.att) + (size_t)q_off * hqw * es,
@@ -1445,8 +1472,8 @@ static akvs_status decode_step(const int32_t *token, int32_t n_past, const void 
   const int hqw = m->n_q_heads * hd, kvw = hkv * hd, qkvw = hqw + 2 * kvw;
   const size_t es = es_of(m->dtype);
   const size_t layer_bytes = (size_t)cache_rows * kvw * es;
-  LAUNCH(AKVS_K_OTHER, launch_rope_table(n_past, 1, hd, (double)m->rope_theta, b.rope, stream));
-  LAUNCH(AKVS_K_OTHER, launch_embed(token, 1, embed, m->dtype, m->vocab, D, b.h, stream));
+  LAUNCH(AKVS_K_OTHER, launch_setup(setup_of(m, token, 1, embed, b.h, n_past, 1, b.rope),
+                                    m->dtype, stream));
   for (int l = 0; l < m->n_layers; ++l) {
     char *kl = reinterpret_cast<char *>(k_cache) + l * layer_bytes;
     char *vl = reinterpret_cast<char *>(v_cache) + l * layer_bytes;

@@ -133,15 +133,20 @@ static inline AttnEqShape attn_eq_shape(int rows, int hq, int hkv, int n_keys, i
 // (tile, range) are numbered by the tile's range length, longest first (equal lengths:
 // later tile first), a tile's ranges together. plan[0] = {tiles, items, max_t c_t},
 // plan[1 + t] = {c_t, first item of tile t, kt_t} (c_t = 0 past the last tile).
-__global__ __launch_bounds__(64) void k_attn_plan(const int32_t *pos, int pos0, int rows,
-                                                  const int32_t *rows_dev,
-                                                  const int32_t *row_base, int n_keys, int rb,
-                                                  int budget, int max_pc, int pack, int4 *plan) {
+struct PlanArgs {
+  AttnPlanReq r;
+  int rb, budget, max_pc, pack;
+};
+__global__ __launch_bounds__(64) void k_attn_plan(PlanArgs p0, PlanArgs p1, int n_keys) {
+  const PlanArgs a = blockIdx.x ? p1 : p0;
+  const int rb = a.rb, budget = a.budget, max_pc = a.max_pc, pack = a.pack, pos0 = a.r.pos0;
+  const int32_t *pos = a.r.pos;
+  int4 *plan = reinterpret_cast<int4 *>(a.r.plan);
   const int lane = threadIdx.x;
-  int R = rows;
-  if (rows_dev) R = min(R, *rows_dev);
+  int R = a.r.rows;
+  if (a.r.rows_dev) R = min(R, *a.r.rows_dev);
   R *= pack;  // (row, head) pairs
-  if (row_base && pos) pos += *row_base;
+  if (a.r.row_base && pos) pos += *a.r.row_base;
   const int nt = (R + rb - 1) / rb;
   int kt = 0;
   if (lane < nt) {
@@ -931,15 +936,18 @@ int attn_part_splits(int rows, int hq, int hkv, int hd, int n_keys) {
   return e.use ? std::max(sp, most) : sp;
 }
 
-hipError_t launch_attention_plan(const int32_t *pos, int pos0, int rows, const int32_t *rows_dev,
-                                 int n_keys, int hq, int hkv, int hd, int dtype,
-                                 long long part_rows, int32_t *plan, hipStream_t s,
-                                 const int32_t *row_base) {
-  const AttnEqShape e =
-      attn_eq_shape(rows, hq, hkv, n_keys, hd, dtype, part_rows, gemm_cu_count());
-  if (!e.use || !plan) return hipSuccess;  // launch_attention will not read it either
-  hipLaunchKernelGGL(k_attn_plan, dim3(1), dim3(64), 0, s, pos, pos0, rows, rows_dev, row_base,
-                     n_keys, e.rb, e.budget, e.max_pc, e.pack, reinterpret_cast<int4 *>(plan));
+hipError_t launch_attention_plan(const AttnPlanReq *req, int n, int n_keys, int hq, int hkv,
+                                 int hd, int dtype, long long part_rows, hipStream_t s) {
+  PlanArgs p[2] = {};
+  int used = 0;
+  for (int i = 0; i < n; ++i) {
+    const AttnEqShape e =
+        attn_eq_shape(req[i].rows, hq, hkv, n_keys, hd, dtype, part_rows, gemm_cu_count());
+    // (launch_attention will not read a plan that is not used either)
+    if (e.use && req[i].plan) p[used++] = {req[i], e.rb, e.budget, e.max_pc, e.pack};
+  }
+  if (used == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_attn_plan, dim3(used), dim3(64), 0, s, p[0], p[1], n_keys);
   return hipGetLastError();
 }
 

@@ -3,57 +3,81 @@
 
 namespace akvs {
 
-// table[p][k] = (cos, sin)(p * theta^(-2k/hd)); angle and trig in fp64.
-__global__ void k_rope_table(int p0, int n_pos, int half, int hd, double theta, float2 *table) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_pos * half) return;
-  const int row = i / half, k = i - row * half;
-  const int p = p0 + row;
+// Rotary table, table[p][k] = (cos, sin)(p * theta^(-2k/hd)); angle and trig in fp64. A thread
+// makes ROPE_ROWS rows of one k, so that the fp64 power is formed once for them.
+constexpr int ROPE_ROWS = 4;
+__host__ __device__ __forceinline__ int rope_blocks(int n_pos, int half) {
+  return (int)(((long long)((n_pos + ROPE_ROWS - 1) / ROPE_ROWS) * half + 255) / 256);
+}
+__device__ __forceinline__ void rope_rows(int block, int p0, int n_pos, int half, int hd,
+                                          double theta, float2 *table) {
+  const long long i = (long long)block * 256 + threadIdx.x;
+  const int r0 = (int)(i / half) * ROPE_ROWS, k = (int)(i % half);
+  if (r0 >= n_pos) return;
   const double inv = pow(theta, (-2.0 * (double)k) / (double)hd);
-  const double a = (double)p * inv;
-  double sn, cs;
-  sincos(a, &sn, &cs);
-  table[i] = make_float2((float)cs, (float)sn);
+  for (int r = r0; r < min(r0 + ROPE_ROWS, n_pos); ++r) {
+    double sn, cs;
+    sincos((double)(p0 + r) * inv, &sn, &cs);
+    table[(size_t)r * half + k] = make_float2((float)cs, (float)sn);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_rope_table(int p0, int n_pos, int half, int hd,
+                                                    double theta, float2 *table) {
+  rope_rows(blockIdx.x, p0, n_pos, half, hd, theta, table);
 }
 
 hipError_t launch_rope_table(int p0, int n_pos, int head_dim, double theta, float *table,
                              hipStream_t s) {
   const int half = head_dim / 2;
-  const int total = n_pos * half;
-  if (total == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_rope_table, dim3((total + 255) / 256), dim3(256), 0, s, p0, n_pos, half,
-                     head_dim, theta, reinterpret_cast<float2 *>(table));
+  if (n_pos == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_rope_table, dim3(rope_blocks(n_pos, half)), dim3(256), 0, s, p0, n_pos,
+                     half, head_dim, theta, reinterpret_cast<float2 *>(table));
   return hipGetLastError();
 }
 
+// What a whole call needs before its first layer, in one launch (each is a few us of work and
+// a launch about 4): blocks [0, n) one embedding row each, then the unit tables (one block per
+// unit), then the rotary table.
 template <typename TE>
-__global__ void k_embed(const int32_t *tok, int n, const TE *embed, int vocab, int D, float *h) {
-  const int t = blockIdx.x;
-  if (t >= n) return;
-  const int id = tok[t];
-  float *dst = h + (size_t)t * D;
-  const bool ok = id >= 0 && id < vocab;
-  const TE *src = embed + (size_t)(ok ? id : 0) * D;
-  for (int e = threadIdx.x * 8; e < D; e += blockDim.x * 8) {
-    float v[8];
-    load8(src + e, v);
-    if (!ok) {
+__global__ __launch_bounds__(256) void k_setup(Setup a) {
+  int b = blockIdx.x;
+  if (b < a.n) {
+    const int id = a.tok[b];
+    float *dst = a.h + (size_t)b * a.D;
+    const bool ok = id >= 0 && id < a.vocab;
+    const TE *src = reinterpret_cast<const TE *>(a.embed) + (size_t)(ok ? id : 0) * a.D;
+    for (int e = threadIdx.x * 8; e < a.D; e += 256 * 8) {
+      float v[8];
+      load8(src + e, v);
+      if (!ok) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = 0.f;
+        for (int i = 0; i < 8; ++i) v[i] = 0.f;
+      }
+      store8(dst + e, v);
     }
-    store8(dst + e, v);
+    return;
   }
+  b -= a.n;
+  if (b < a.n_chunks) {
+    const int4 mc = reinterpret_cast<const int4 *>(a.meta)[b];
+    for (int j = threadIdx.x; j < mc.y; j += 256) {
+      a.tok_delta[mc.x + j] = mc.x;
+      a.tok_chunk[mc.x + j] = b;
+    }
+    return;
+  }
+  rope_rows(b - a.n_chunks, a.p0, a.n_pos, a.hd >> 1, a.hd, a.theta,
+            reinterpret_cast<float2 *>(a.rope));
 }
 
-hipError_t launch_embed(const int32_t *tok, int n, const void *embed, int dtype, int vocab, int D,
-                        float *h, hipStream_t s) {
-  if (n == 0) return hipSuccess;
+hipError_t launch_setup(const Setup &a, int dtype, hipStream_t s) {
+  const int blocks = a.n + a.n_chunks + (a.n_pos > 0 ? rope_blocks(a.n_pos, a.hd >> 1) : 0);
+  if (blocks == 0) return hipSuccess;
   if (dtype == AKVS_BF16)
-    hipLaunchKernelGGL(k_embed<bf16_t>, dim3(n), dim3(128), 0, s, tok, n,
-                       reinterpret_cast<const bf16_t *>(embed), vocab, D, h);
+    hipLaunchKernelGGL(k_setup<bf16_t>, dim3(blocks), dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL(k_embed<float>, dim3(n), dim3(128), 0, s, tok, n,
-                       reinterpret_cast<const float *>(embed), vocab, D, h);
+    hipLaunchKernelGGL(k_setup<float>, dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -180,24 +204,25 @@ hipError_t launch_gather_rows(const float *src, int n_src, const int32_t *idx, i
   return hipGetLastError();
 }
 
-// dst[i] = src[base + *n_dev - n + i] for i < n (rows of row_bytes bytes, a multiple of 16).
-__global__ void k_copy_tail_rows(const char *src, size_t row_bytes, int n, const int32_t *n_dev,
-                                 char *dst, const int32_t *src_base) {
+// For two row sets of the same rows (blockIdx.y): dst[i] = src[base + *n_dev - n + i] for
+// i < n (rows of a multiple of 16 bytes).
+__global__ void k_copy_tail_rows(TailRows a, TailRows b, int n, const int32_t *n_dev,
+                                 const int32_t *src_base) {
+  const TailRows t = blockIdx.y ? b : a;
   const int i = blockIdx.x;
   const int j = *n_dev - n + i;
   if (i >= n || j < 0) return;
   const size_t row = (size_t)(src_base ? *src_base : 0) + j;
-  const uint4 *a = reinterpret_cast<const uint4 *>(src + row * row_bytes);
-  uint4 *b = reinterpret_cast<uint4 *>(dst + (size_t)i * row_bytes);
-  for (size_t e = threadIdx.x; e < row_bytes / 16; e += blockDim.x) b[e] = a[e];
+  const uint4 *x = reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(t.src) +
+                                                   row * t.row_bytes);
+  uint4 *y = reinterpret_cast<uint4 *>(reinterpret_cast<char *>(t.dst) + (size_t)i * t.row_bytes);
+  for (size_t e = threadIdx.x; e < t.row_bytes / 16; e += blockDim.x) y[e] = x[e];
 }
 
-hipError_t launch_copy_tail_rows(const void *src, size_t row_bytes, int n, const int32_t *n_dev,
-                                 void *dst, hipStream_t s, const int32_t *src_base) {
+hipError_t launch_copy_tail_rows(const TailRows &a, const TailRows &b, int n,
+                                 const int32_t *n_dev, hipStream_t s, const int32_t *src_base) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_copy_tail_rows, dim3(n), dim3(256), 0, s,
-                     reinterpret_cast<const char *>(src), row_bytes, n, n_dev,
-                     reinterpret_cast<char *>(dst), src_base);
+  hipLaunchKernelGGL(k_copy_tail_rows, dim3(n, 2), dim3(256), 0, s, a, b, n, n_dev, src_base);
   return hipGetLastError();
 }
 
@@ -241,24 +266,6 @@ __global__ void k_copy_int(const int32_t *src, int32_t *dst) {
 
 hipError_t launch_copy_int(const int32_t *src, int32_t *dst, hipStream_t s) {
   hipLaunchKernelGGL(k_copy_int, dim3(1), dim3(64), 0, s, src, dst);
-  return hipGetLastError();
-}
-
-__global__ void k_token_setup(const int4 *meta, int n_chunks, int32_t *tok_delta,
-                              int32_t *tok_chunk) {
-  const int c = blockIdx.x;
-  if (c >= n_chunks) return;
-  const int4 mc = meta[c];
-  for (int j = threadIdx.x; j < mc.y; j += blockDim.x) {
-    tok_delta[mc.x + j] = mc.x;
-    tok_chunk[mc.x + j] = c;
-  }
-}
-
-hipError_t launch_token_setup(const int32_t *meta, int n_chunks, int32_t *tok_delta,
-                              int32_t *tok_chunk, hipStream_t s) {
-  hipLaunchKernelGGL(k_token_setup, dim3(n_chunks), dim3(256), 0, s,
-                     reinterpret_cast<const int4 *>(meta), n_chunks, tok_delta, tok_chunk);
   return hipGetLastError();
 }
 

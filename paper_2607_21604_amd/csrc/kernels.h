@@ -9,9 +9,24 @@ namespace akvs {
 // table row i holds position p0 + i.
 hipError_t launch_rope_table(int p0, int n_pos, int head_dim, double theta, float *table,
                              hipStream_t s);
-// h[t][:] = embed[tok[t]][:] (fp32), t < n; ids outside [0, vocab) give a zero row.
-hipError_t launch_embed(const int32_t *tok, int n, const void *embed, int dtype, int vocab, int D,
-                        float *h, hipStream_t s);
+// The parts of a whole call before its first layer, in one launch (each may be empty):
+//  - h[t][:] = embed[tok[t]][:] (fp32), t < n; ids outside [0, vocab) give a zero row;
+//  - per unit token t of n_chunks units: tok_delta[t] = s_i, tok_chunk[t] = i (meta: device);
+//  - the rotary table of n_pos positions from p0, as launch_rope_table.
+struct Setup {
+  const int32_t *tok;
+  int n;
+  const void *embed;
+  int vocab, D;
+  float *h;
+  const int32_t *meta;
+  int n_chunks;
+  int32_t *tok_delta, *tok_chunk;
+  int p0, n_pos, hd;
+  double theta;
+  float *rope;
+};
+hipError_t launch_setup(const Setup &a, int dtype, hipStream_t s);
 // out[i] = RMSNorm(h[src(i)]) * gain, i < rows (and < *rows_dev if given).
 // src(i) = i + (base_dev ? *base_dev - rows : 0)  (base_dev selects the last `rows` rows).
 hipError_t launch_rmsnorm(const float *h, int ldh, int rows, const int32_t *rows_dev,
@@ -23,9 +38,15 @@ hipError_t launch_gather_rows(const float *src, int n_src, const int32_t *idx, i
                               const int32_t *n_dev, int D, float *dst, hipStream_t s,
                               const int32_t *dst_base = nullptr);
 // dst row i = src row (base + *n_dev - n + i), i < n: the last n of *n_dev rows that start
-// at row base = *src_base (or 0).
-hipError_t launch_copy_tail_rows(const void *src, size_t row_bytes, int n, const int32_t *n_dev,
-                                 void *dst, hipStream_t s, const int32_t *src_base = nullptr);
+// at row base = *src_base (or 0), of two row sets at once.
+struct TailRows {
+  const void *src;
+  size_t row_bytes;
+  void *dst;
+};
+hipError_t launch_copy_tail_rows(const TailRows &a, const TailRows &b, int n,
+                                 const int32_t *n_dev, hipStream_t s,
+                                 const int32_t *src_base = nullptr);
 // row_off[b] = n_rows[0] + ... + n_rows[b-1] for b = 0..B (a batch's row segments).
 hipError_t launch_batch_layout(const int32_t *n_rows, int B, int32_t *row_off, hipStream_t s);
 // dst[*dst_base + i] = src[i] for i < min(cap, *n_dev).
@@ -33,10 +54,6 @@ hipError_t launch_copy_ints_at(const int32_t *src, int cap, const int32_t *n_dev
                                const int32_t *dst_base, hipStream_t s);
 // dst[0] = src[0] on the device.
 hipError_t launch_copy_int(const int32_t *src, int32_t *dst, hipStream_t s);
-// per unit token t < T_c: tok_delta[t] = s_i, tok_chunk[t] = i.
-hipError_t launch_token_setup(const int32_t *meta, int n_chunks, int32_t *tok_delta,
-                              int32_t *tok_chunk, hipStream_t s);
-
 // ---- k_reuse.hip --------------------------------------------------------------------
 hipError_t launch_divergence(const void *k_fresh, const void *v_fresh, int fresh_dtype,
                              CacheLayer cache, int n_tokens, int hkv, int hd,
@@ -129,16 +146,20 @@ hipError_t launch_attention(const void *q, const int32_t *pos, int pos0, int row
                             int hq, int hkv, int hd, int dtype, void *out, float *part_o,
                             float *part_ml, long long part_rows, hipStream_t s,
                             const int32_t *row_base = nullptr, const int32_t *plan = nullptr);
-// Plan of a split over the same rows (positions, row bound, live count, row_base as the
-// launch_attention call that reads it; plan: kAttnPlanInts int32 of device memory, 16-byte
-// aligned). Nothing is launched, and launch_attention ignores the plan, where the call's
-// shape does not use one. The plan depends only on the rows' positions and n_keys: one
-// plan serves every layer over the same rows.
+// Plans of splits over row sets (positions, row bound, live count, row_base as the
+// launch_attention call that reads the plan; plan: kAttnPlanInts int32 of device memory,
+// 16-byte aligned) over the same n_keys keys, one or two in one launch. Nothing is launched,
+// and launch_attention ignores the plan, where the call's shape does not use one. A plan
+// depends only on the rows' positions and n_keys: one serves every layer over the same rows.
 constexpr int kAttnPlanInts = 4 * 65;
-hipError_t launch_attention_plan(const int32_t *pos, int pos0, int rows, const int32_t *rows_dev,
-                                 int n_keys, int hq, int hkv, int hd, int dtype,
-                                 long long part_rows, int32_t *plan, hipStream_t s,
-                                 const int32_t *row_base = nullptr);
+struct AttnPlanReq {
+  const int32_t *pos;
+  int pos0, rows;
+  const int32_t *rows_dev, *row_base;
+  int32_t *plan;
+};
+hipError_t launch_attention_plan(const AttnPlanReq *req, int n, int n_keys, int hq, int hkv,
+                                 int hd, int dtype, long long part_rows, hipStream_t s);
 // number of key splits launch_attention uses for `rows` rows over n_keys keys
 int attn_splits(int rows, int hq, int hkv, int n_keys);
 // partial slots per row that the part_o / part_ml buffers of such a call should hold
