@@ -479,23 +479,37 @@ Setup setup_units(Setup a, const int32_t *meta, int n_chunks, int32_t *tok_delta
   return a;
 }
 
-// Attention output projection + MLP over rows (h updated in place).
+// h += A W^T over rows (A [rows][K], W [D][K]), then with a gain x = RMSNorm(h) * gain.
+akvs_status resid_norm(const akvs_model_cfg *m, const void *A, int K, const void *W, float *h,
+                       int rows, const int32_t *rows_dev, const void *gain, void *x,
+                       float *gpart, hipStream_t stream, int rows_min) {
+  const int D = m->d_model;
+  const Epi e = simple_epi(EPI_RESID, h, D, AKVS_F32);
+  const NormAfter na{gain, m->rms_eps, x};
+  bool normed = false;
+  LAUNCH(AKVS_K_GEMM, launch_gemm(A, K, W, K, rows, D, K, rows_dev, m->dtype, e, stream, gpart,
+                                  rows_min));
+  LAUNCH(AKVS_K_OTHER, launch_gemm_fixup(A, K, W, K, rows, D, K, rows_dev, m->dtype, e, stream,
+                                         gpart, rows_min, gain ? &na : nullptr, &normed));
+  if (gain && !normed)
+    LAUNCH(AKVS_K_NORM, launch_rmsnorm(h, D, rows, rows_dev, nullptr, gain, m->dtype, D,
+                                       m->rms_eps, x, m->dtype, D, stream));
+  return AKVS_OK;
+}
+
+// Attention output projection + MLP over rows (h updated in place). With next_norm (the next
+// layer's attn_norm) x ends as the normalised rows that layer starts from.
 akvs_status out_mlp(const akvs_model_cfg *m, const akvs_layer_w &w, float *h, int rows,
                     const int32_t *rows_dev, const void *att, void *x, void *act, float *gpart,
-                    hipStream_t stream, int rows_min = 0) {
+                    hipStream_t stream, int rows_min = 0, const void *next_norm = nullptr) {
   const int D = m->d_model, F = m->ffn_dim, hqw = m->n_q_heads * m->head_dim;
-  GEMM(att, hqw, w.w_o, hqw, rows, D, hqw, rows_dev, m->dtype,
-                                  simple_epi(EPI_RESID, h, D, AKVS_F32), stream, gpart,
-                                  rows_min);
-  LAUNCH(AKVS_K_NORM, launch_rmsnorm(h, D, rows, rows_dev, nullptr, w.mlp_norm, m->dtype, D,
-                                     m->rms_eps, x, m->dtype, D, stream));
+  akvs_status st = resid_norm(m, att, hqw, w.w_o, h, rows, rows_dev, w.mlp_norm, x, gpart, stream,
+                              rows_min);
+  if (st) return st;
   GEMM(x, D, w.w_gate_up, D, rows, F, D, rows_dev, m->dtype,
                                   simple_epi(EPI_SWIGLU, act, F, m->dtype), stream, gpart,
                                   rows_min);
-  GEMM(act, F, w.w_down, F, rows, D, F, rows_dev, m->dtype,
-                                  simple_epi(EPI_RESID, h, D, AKVS_F32), stream, gpart,
-                                  rows_min);
-  return AKVS_OK;
+  return resid_norm(m, act, F, w.w_down, h, rows, rows_dev, next_norm, x, gpart, stream, rows_min);
 }
 
 // Attention split plan of full_layer over n rows (into lb.plan, read by every such layer).
@@ -507,14 +521,16 @@ hipError_t plan_full_layers(const akvs_model_cfg *m, int n, const LayerBufs &lb,
 }
 
 // One ordinary causal layer over n consecutive rows at positions pos0.. (keys written to
-// k_dst / v_dst rows 0..n-1). With planned = true, plan_full_layers(m, n, lb) ran before.
+// k_dst / v_dst rows 0..n-1). With planned = true, plan_full_layers(m, n, lb) ran before; unless
+// this is the first layer, lb.x holds its normalised input (the layer before had next_norm).
 akvs_status full_layer(const akvs_model_cfg *m, const akvs_layer_w &w, float *h, int n, int pos0,
                        const float *rope, const LayerBufs &lb, void *k_dst, void *v_dst,
-                       hipStream_t stream, bool planned) {
+                       hipStream_t stream, bool planned, bool first, const void *next_norm) {
   const int D = m->d_model;
   const int qkvw = (m->n_q_heads + 2 * m->n_kv_heads) * m->head_dim;
-  LAUNCH(AKVS_K_NORM, launch_rmsnorm(h, D, n, nullptr, nullptr, w.attn_norm, m->dtype, D,
-                                     m->rms_eps, lb.x, m->dtype, D, stream));
+  if (first)
+    LAUNCH(AKVS_K_NORM, launch_rmsnorm(h, D, n, nullptr, nullptr, w.attn_norm, m->dtype, D,
+                                       m->rms_eps, lb.x, m->dtype, D, stream));
   GEMM(lb.x, D, w.w_qkv, D, n, qkvw, D, nullptr, m->dtype,
                                   qkv_epi(m, lb.q, k_dst, v_dst, nullptr, pos0, 0, rope, n, pos0),
                                   stream, lb.gpart);
@@ -522,7 +538,7 @@ akvs_status full_layer(const akvs_model_cfg *m, const akvs_layer_w &w, float *h,
                                             m->n_q_heads, m->n_kv_heads, m->head_dim, m->dtype,
                                             lb.att, lb.part_o, lb.part_ml, lb.part_rows, stream,
                                             nullptr, planned ? lb.plan : nullptr));
-  return out_mlp(m, w, h, n, nullptr, lb.att, lb.x, lb.act, lb.gpart, stream);
+  return out_mlp(m, w, h, n, nullptr, lb.att, lb.x, lb.act, lb.gpart, stream, 0, next_norm);
 }
 
 // ---- batched reuse prefill ---------------------------------------------------------------
@@ -1025,7 +1041,8 @@ akvs_status akvs_full_prefill(const int32_t *tokens, int32_t n_tokens, int32_t p
   for (int l = 0; l < m->n_layers; ++l) {
     st = full_layer(m, lw[l], b.h, n_tokens, pos0, b.rope, b.lb,
                     reinterpret_cast<char *>(k_out) + l * kvl,
-                    reinterpret_cast<char *>(v_out) + l * kvl, stream, true);
+                    reinterpret_cast<char *>(v_out) + l * kvl, stream, true, l == 0,
+                    l + 1 < m->n_layers ? lw[l + 1].attn_norm : nullptr);
     if (st) return st;
   }
   if (h_out)
@@ -1088,7 +1105,8 @@ akvs_status akvs_reuse_prefill(const int32_t *tokens, const void *embed, const a
   if (c > 0) LAUNCH(AKVS_K_OTHER, plan_full_layers(m, T, b.lb, stream));
   for (int l = 0; l < c; ++l) {
     st = full_layer(m, lw[l], b.h_full, T, 0, b.rope, b.lb, k_corr + l * corr_layer,
-                    v_corr + l * corr_layer, stream, true);
+                    v_corr + l * corr_layer, stream, true, l == 0,
+                    l + 1 < c ? lw[l + 1].attn_norm : nullptr);
     if (st) return st;
   }
   // check layer: fresh K/V of every unit token, divergence against the re-rotated cache
@@ -1120,8 +1138,9 @@ akvs_status akvs_reuse_prefill(const int32_t *tokens, const void *embed, const a
   const int qkvw = hqw + 2 * kvw;
   for (int l = c; l < L; ++l) {
     CacheLayer cl = cache_layer(cache, l, Tc, hkv, hd);
-    LAUNCH(AKVS_K_NORM, launch_rmsnorm(b.h_probe, D, cap, b.n_rows, nullptr, lw[l].attn_norm,
-                                       m->dtype, D, m->rms_eps, b.lb.x, m->dtype, D, stream));
+    if (l == c)  // later layers' rows were normalised by the layer before
+      LAUNCH(AKVS_K_NORM, launch_rmsnorm(b.h_probe, D, cap, b.n_rows, nullptr, lw[l].attn_norm,
+                                         m->dtype, D, m->rms_eps, b.lb.x, m->dtype, D, stream));
     GEMM(b.lb.x, D, lw[l].w_qkv, D, cap, qkvw, D, b.n_rows, m->dtype,
                        qkv_epi(m, b.lb.q, b.k_fresh, b.v_fresh, b.rows, 0, 0, b.rope, T, 0),
                        stream, b.lb.gpart, (int)mt.row_min);
@@ -1140,7 +1159,7 @@ akvs_status akvs_reuse_prefill(const int32_t *tokens, const void *embed, const a
                                                 b.lb.part_o, b.lb.part_ml, b.lb.part_rows,
                                                 stream, nullptr, b.plan_rows));
       st = out_mlp(m, lw[l], b.h_probe, cap, b.n_rows, b.lb.att, b.lb.x, b.lb.act, b.lb.gpart,
-                   stream, (int)mt.row_min);
+                   stream, (int)mt.row_min, lw[l + 1].attn_norm);
       if (st) return st;
       continue;
     }
@@ -1237,7 +1256,8 @@ akvs_status akvs_reuse_prefill_batch(const int32_t *const *tokens, int32_t batch
     for (int l = 0; l < c; ++l) {
       if (l == 0) LAUNCH(AKVS_K_OTHER, plan_full_layers(m, T, b.lb_full, stream));
       st = full_layer(m, lw[l], r.h_full, T, 0, b.rope, b.lb_full, k_corr + l * corr_layer,
-                      v_corr + l * corr_layer, stream, true);
+                      v_corr + l * corr_layer, stream, true, l == 0,
+                    l + 1 < c ? lw[l + 1].attn_norm : nullptr);
       if (st) return st;
     }
     if (!no_prefix) {
@@ -1272,8 +1292,9 @@ akvs_status akvs_reuse_prefill_batch(const int32_t *const *tokens, int32_t batch
                                                m->dtype, b.lb.part_rows, stream));
   }
   for (int l = c; l < L; ++l) {
-    LAUNCH(AKVS_K_NORM, launch_rmsnorm(b.h_probe, D, cap_sum, M_dev, nullptr, lw[l].attn_norm,
-                                       m->dtype, D, m->rms_eps, b.lb.x, m->dtype, D, stream));
+    if (l == c)  // later layers' rows were normalised by the layer before
+      LAUNCH(AKVS_K_NORM, launch_rmsnorm(b.h_probe, D, cap_sum, M_dev, nullptr, lw[l].attn_norm,
+                                         m->dtype, D, m->rms_eps, b.lb.x, m->dtype, D, stream));
     GEMM(b.lb.x, D, lw[l].w_qkv, D, cap_sum, qkvw, D, M_dev, m->dtype,
          qkv_epi(m, b.lb.q, b.k_fresh, b.v_fresh, b.pos, 0, 0, b.rope, T_max, 0), stream,
          b.lb.gpart, (int)pl.min_sum);
@@ -1319,7 +1340,7 @@ akvs_status akvs_reuse_prefill_batch(const int32_t *const *tokens, int32_t batch
     }
     if (!last) {
       st = out_mlp(m, lw[l], b.h_probe, cap_sum, M_dev, b.lb.att, b.lb.x, b.lb.act, b.lb.gpart,
-                   stream, (int)pl.min_sum);
+                   stream, (int)pl.min_sum, lw[l + 1].attn_norm);
     } else {
       st = out_mlp(m, lw[l], b.h_last, q_sum, nullptr, b.lb.att, b.lb.x, b.lb.act, b.lb.gpart,
                    stream);

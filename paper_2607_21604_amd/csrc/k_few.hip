@@ -312,6 +312,65 @@ __global__ __launch_bounds__(256) void k_few_sum(const float *__restrict__ part,
       make_float4(old.x + a.x, old.y + a.y, old.z + a.z, old.w + a.w);
 }
 
+// The same sum by whole rows, followed by the RMSNorm of the row that the next projection
+// reads: out = RMSNorm(h) * gain, with the element order and arithmetic of k_rmsnorm. One block
+// per row; saves the norm's own launch and its read of h (203 rows of width 3072: 5.3 + 5.1
+// us as two launches, 5.9 here).
+constexpr int kSumNormChunks = 4;  // 2048 columns each
+__global__ __launch_bounds__(256) void k_few_sum_norm(const float *__restrict__ part, int splits,
+                                                      int M, int N, const int32_t *m_dev,
+                                                      float *__restrict__ h, int ldo,
+                                                      const bf16_t *__restrict__ gain, float eps,
+                                                      bf16_t *__restrict__ out) {
+  __shared__ float red[4];
+  const int r = blockIdx.x;
+  if (r >= (m_dev ? min(M, *m_dev) : M)) return;
+  float *row = h + (size_t)r * ldo;
+  float v[kSumNormChunks][8], g[kSumNormChunks][8];
+  float ss = 0.f;
+#pragma unroll
+  for (int c = 0; c < kSumNormChunks; ++c) {
+    const int e = threadIdx.x * 8 + c * 2048;
+    if (e >= N) continue;
+    load8(gain + e, g[c]);
+    load8(row + e, v[c]);
+    const float *p = part + (size_t)r * N + e;
+    float q[kFewMaxSplits][8];
+#pragma unroll
+    for (int s = 0; s < kFewMaxSplits; ++s)
+      if (s < splits) load8(p + (size_t)s * M * N, q[s]);
+#pragma unroll
+    for (int s = 1; s < kFewMaxSplits; ++s)
+      if (s < splits) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) q[0][i] += q[s][i];
+      }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[c][i] += q[0][i];
+    store8(row + e, v[c]);
+  }
+#pragma unroll
+  for (int c = 0; c < kSumNormChunks; ++c) {
+    if (threadIdx.x * 8 + c * 2048 < N) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) ss = fmaf(v[c][i], v[c][i], ss);
+    }
+  }
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  const float tot = (red[0] + red[1]) + (red[2] + red[3]);
+  const float inv = 1.0f / sqrtf(tot / (float)N + eps);
+#pragma unroll
+  for (int c = 0; c < kSumNormChunks; ++c) {
+    const int e = threadIdx.x * 8 + c * 2048;
+    if (e >= N) continue;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[c][i] = v[c][i] * inv * g[c][i];
+    store8(out + (size_t)r * N + e, v[c]);
+  }
+}
+
 }  // namespace
 
 template <int BM, int BN, int BK, int NST>
@@ -346,7 +405,15 @@ hipError_t launch_few(int tile, int splits, const void *A, int lda, const void *
 }
 
 hipError_t launch_few_sum(int splits, int M, int N, const int32_t *m_dev, const Epi &e,
-                          const float *part, hipStream_t s) {
+                          const float *part, hipStream_t s, const NormAfter *norm, bool *normed) {
+  if (norm && N <= kSumNormChunks * 2048 && N % 8 == 0) {
+    hipLaunchKernelGGL(k_few_sum_norm, dim3(M), dim3(256), 0, s, part, splits, M, N, m_dev,
+                       reinterpret_cast<float *>(e.out), e.ldo,
+                       reinterpret_cast<const bf16_t *>(norm->gain), norm->eps,
+                       reinterpret_cast<bf16_t *>(norm->out));
+    *normed = true;
+    return hipGetLastError();
+  }
   const long long n4 = (long long)M * N / 4;
   hipLaunchKernelGGL(k_few_sum, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, part, splits,
                      M, N, m_dev, reinterpret_cast<float *>(e.out), e.ldo);

@@ -1315,14 +1315,15 @@ hipError_t launch_gemm(const void *A, int lda, const void *B, int ldb, int M, in
 
 hipError_t launch_gemm_fixup(const void *, int lda, const void *, int ldb, int M, int N, int K,
                              const int32_t *m_dev, int dtype, const Epi &epi, hipStream_t s,
-                             float *part, int m_min) {
+                             float *part, int m_min, const NormAfter *norm, bool *normed) {
   if (M == 0 || N == 0 || dtype != AKVS_BF16) return hipSuccess;
   const size_t b_rows = epi.mode == EPI_SWIGLU ? 2 * (size_t)N : (size_t)N;
   const bool fits = (size_t)M * lda * 2 < (1u << 31) && b_rows * ldb * 2 < (1u << 31);
   if (fits) {
     const FewChoice f = few_choice(M, N, K, m_dev, epi, part, m_min);
     if (f.tile >= 0)
-      return f.splits > 1 ? launch_few_sum(f.splits, M, N, m_dev, epi, part, s) : hipSuccess;
+      return f.splits > 1 ? launch_few_sum(f.splits, M, N, m_dev, epi, part, s, norm, normed)
+                          : hipSuccess;
     const W8Choice c = w8_choice(M, N, K, m_dev, epi.mode, part, m_min);
     if (!c.any_split) return hipSuccess;
     const int bn_out = epi.mode == EPI_SWIGLU ? kW8SplitBN / 2 : kW8SplitBN;

@@ -118,10 +118,18 @@ hipError_t launch_gemm(const void *A, int lda, const void *B, int ldb, int M, in
                        const int32_t *m_dev, int dtype, const Epi &epi, hipStream_t s,
                        float *part = nullptr, int m_min = 0);
 // Second kernel of a K-split GEMM (same arguments as launch_gemm, launched right after it on
-// the same stream); launches nothing when the first one cannot have split.
+// the same stream); launches nothing when the first one cannot have split. With `norm` (bf16
+// RESID products over whole rows) it may form the RMSNorm of the finished rows as well:
+// *normed then becomes true.
+struct NormAfter {
+  const void *gain;  // bf16 [N]
+  float eps;
+  void *out;         // bf16 [M][N]
+};
 hipError_t launch_gemm_fixup(const void *A, int lda, const void *B, int ldb, int M, int N,
                              int K, const int32_t *m_dev, int dtype, const Epi &epi,
-                             hipStream_t s, float *part = nullptr, int m_min = 0);
+                             hipStream_t s, float *part = nullptr, int m_min = 0,
+                             const NormAfter *norm = nullptr, bool *normed = nullptr);
 size_t gemm_part_floats(int M, int N, int K, int mode);
 // ---- k_few.hip ----------------------------------------------------------------------
 // The few-row GEMM with tile `tile` of few_tile (k_gemm.hip picks it); splits > 1: RESID only,
@@ -131,7 +139,7 @@ hipError_t launch_few(int tile, int splits, const void *A, int lda, const void *
                       int N, int K, const int32_t *m_dev, const Epi &e, float *part,
                       hipStream_t s);
 hipError_t launch_few_sum(int splits, int M, int N, const int32_t *m_dev, const Epi &e,
-                          const float *part, hipStream_t s);
+                          const float *part, hipStream_t s, const NormAfter *norm, bool *normed);
 int gemm_cu_count();
 
 // ---- k_attn.hip ---------------------------------------------------------------------
