@@ -427,7 +427,7 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
           }
           __builtin_memcpy(&vf[t][db], vw, 16);
         };
-        if (PREF || DIR) {  // every V^T fragment of the block requested up front
+        if (PREF) {  // every V^T fragment of the block requested up front
 #pragma unroll
           for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -448,6 +448,17 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
                    : *reinterpret_cast<const bf16x8_t *>(
                          krow + (DIR ? ((2 * ks + hi) ^ (lane & 15)) * 8 : ks * 16));
           sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], sc, 0, 0, 0);
+        }
+        if constexpr (DIR) {
+          // V^T fragments behind the K fragments: LDS answers in order, so requested before the
+          // scores they held up every score MFMA, and the softmax hides them as well (same bits;
+          // 5534 rows of the 32B heads over 16128 keys 880 -> 864 us, 1413 of 3B over 4516 75 ->
+          // 72.5, 2806 of 7B over 8128 202 -> 198)
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) read_v(t, db);
         }
         if (PREF && st == 0 && sk0 + 32 <= wmax) {
           const bf16_t *knext = ks_ + (32 + (lane & 31)) * KST + hi * 8;
