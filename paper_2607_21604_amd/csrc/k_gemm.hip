@@ -1224,42 +1224,55 @@ static FewChoice few_choice(int M, int N, int K, const int32_t *m_dev, const Epi
   if (epi.mode != EPI_RESID && (epi.mode == EPI_STORE || epi.out_dtype != AKVS_BF16)) return best;
   const int cus = gemm_cu_count(), nk64 = K / 64;
   const bool swiglu = epi.mode == EPI_SWIGLU;
-  // a row count known only on the device lies between the bounds, nearer to the upper one
-  // (two probe sets overlap little): priced at two thirds of the way
+  // A row count known only on the device lies between the bounds, in their upper half (two probe
+  // sets overlap little): priced as the sum over three counts there, since a tile that fits one
+  // of them may need another round at the next (7B output and down projections of about 880
+  // rows, bounds 513 and 1003: 252 tiles of 96 x 128 at two thirds of the way, 280 live: 59
+  // and 261 us against 50 and 202 on the split 8-wave tiles).
   const int lo = m_dev ? std::min(std::max(m_min, 1), M) : M;
-  const int m = lo + 2 * (M - lo) / 3;
+  const int pts[3] = {M, M - (M - lo) / 4, M - (M - lo) / 2}, n_pts = M > lo ? 3 : 1;
   const double w_mb = (swiglu ? 2.0 : 1.0) * N * K * 2e-6;
   auto split_cost = [&](double floats) { return 3.5 + floats * 8e-6 / 6.0; };
   // the 8-wave kernels
-  long long cost;
-  const int w8 = gemm_w8_tile(m, N, epi.mode, cus, &cost);
-  double t_best = 4 + std::max((double)cost * (1.70 / 65536) * nk64, w_mb / (w8 == 4 ? 5.3 : 4.2));
-  const int w8_sp = part ? w8_k_splits(m, N, K, epi.mode, cus) : 1;
-  if (w8_sp > 1) {
-    const int bn_out = swiglu ? kW8SplitBN / 2 : kW8SplitBN;
-    const double tiles = ((m + kW8SplitBM - 1) / kW8SplitBM) * (double)((N + bn_out - 1) / bn_out);
-    t_best = 4 + std::max((double)((nk64 + w8_sp - 1) / w8_sp) * 0.72, w_mb / 3.6) +
-             split_cost(tiles * w8_sp * kW8SplitBM * kW8SplitBN);
+  double t_best = 0;
+  for (int p = 0; p < n_pts; ++p) {
+    const int m = pts[p], w8_sp = part ? w8_k_splits(m, N, K, epi.mode, cus) : 1;
+    if (w8_sp > 1) {
+      const int bn_out = swiglu ? kW8SplitBN / 2 : kW8SplitBN;
+      const double tiles =
+          ((m + kW8SplitBM - 1) / kW8SplitBM) * (double)((N + bn_out - 1) / bn_out);
+      t_best += 4 + std::max((double)((nk64 + w8_sp - 1) / w8_sp) * 0.72, w_mb / 3.6) +
+                split_cost(tiles * w8_sp * kW8SplitBM * kW8SplitBN);
+    } else {
+      long long cost;
+      const int w8 = gemm_w8_tile(m, N, epi.mode, cus, &cost);
+      t_best += 4 + std::max((double)cost * (1.70 / 65536) * nk64, w_mb / (w8 == 4 ? 5.3 : 4.2));
+    }
   }
   for (int i = 0; i < kFewCount; ++i) {
     const FewTile &t = kFewTiles[i];
     if (K % t.bk) continue;
     const int bn_out = swiglu ? t.bn / 2 : t.bn, nk = K / t.bk;
-    const int tiles = ((m + t.bm - 1) / t.bm) * ((N + bn_out - 1) / bn_out);
+    const int n_cols = (N + bn_out - 1) / bn_out;
     int last = 0;
     for (int want = 1; want <= kFewMaxSplits; ++want) {
       const int sp = even_splits(nk, std::min(want, nk));
       if (sp == last) continue;
       last = sp;
       // slices need partials, which are set aside where the 8-wave kernels may split
-      if (sp > 1 && (epi.mode != EPI_RESID || !part || tiles * sp > cus ||
+      if (sp > 1 && (epi.mode != EPI_RESID || !part ||
+                     ((pts[n_pts - 1] + t.bm - 1) / t.bm) * n_cols * sp > cus ||
                      w8_k_splits(1, N, K, epi.mode, cus) < 2 ||
                      (size_t)sp * M * N > (size_t)cus * kW8SplitBM * kW8SplitBN))
         break;
-      const double rounds = (tiles * sp + cus - 1) / cus;
       const double steps = (double)((nk + sp - 1) / sp) * (t.bk / 64);
-      const double us = 4 + std::max(rounds * steps * t.step, w_mb / (rounds > 1 ? 4.4 : 5.3)) +
-                        (sp > 1 ? split_cost((double)sp * m * N) : 0.0);
+      double us = 0;
+      for (int p = 0; p < n_pts; ++p) {
+        const int m = pts[p], tiles = ((m + t.bm - 1) / t.bm) * n_cols;
+        const double rounds = (tiles * sp + cus - 1) / cus;
+        us += 4 + std::max(rounds * steps * t.step, w_mb / (rounds > 1 ? 4.4 : 5.3)) +
+              (sp > 1 ? split_cost((double)sp * m * N) : 0.0);
+      }
       if (us < t_best) {
         t_best = us;
         best = {i, sp};
