@@ -72,9 +72,10 @@ def parse():
     return p.parse_args()
 
 
-GEMM_KERNEL = "k_gemm_bf16"
+GEMM_KERNELS = ("k_gemm_bf16", "k_gemm_few")
 COPY_BYTES = 1 << 30
-GEMM_SOURCE = os.path.join(ROOT, "paper_2607_21604_amd", "csrc", "k_gemm.hip")
+GEMM_SOURCES = [os.path.join(ROOT, "paper_2607_21604_amd", "csrc", f)
+                for f in ("k_gemm.hip", "k_few.hip", "gemm_dev.h")]
 PROFILE_FLAGS = ("--no-cpu-baseline --no-full --no-graph --no-decode --refresh-sweep none "
                  "--batch-sweep none --extra-workloads none")
 
@@ -83,9 +84,9 @@ def traffic_file(workload):
     return os.path.join(ROOT, "profiles", f"k_gemm_bf16_traffic_{workload}_reuse.txt")
 
 
-def source_hash(path=GEMM_SOURCE):
+def source_hash(paths=GEMM_SOURCES):
     import hashlib
-    return hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
+    return hashlib.sha256(b"".join(open(p, "rb").read() for p in paths)).hexdigest()[:16]
 
 
 def traffic_summary(fetch_csv, write_csv, workload, refresh):
@@ -100,7 +101,7 @@ def traffic_summary(fetch_csv, write_csv, workload, refresh):
             if r["Counter_Name"] != counter:
                 continue
             v = float(r["Counter_Value"])
-            if GEMM_KERNEL in r["Kernel_Name"]:
+            if any(k in r["Kernel_Name"] for k in GEMM_KERNELS):
                 gemm.append(v)
             elif "neg_kernel" in r["Kernel_Name"]:
                 copy.append(v)
@@ -150,6 +151,7 @@ def measured_traffic(workload):
 
 
 KERNEL_CLASSES = (("k_gemm_bf16", "GEMM (every k_gemm_bf16* kernel, fixup excluded)"),
+                  ("k_gemm_few", "few-row GEMM (sums of split K excluded)"),
                   ("k_attn_bf16", "attention (without the split merge)"),
                   ("k_attn_combine", "attention split merge"),
                   ("k_correction", "re-rotation + correction"),
@@ -159,7 +161,7 @@ KERNEL_CLASSES = (("k_gemm_bf16", "GEMM (every k_gemm_bf16* kernel, fixup exclud
 
 def trace_summary(path, n_last):
     """Per-kernel durations of a rocprofv3 --kernel-trace CSV of this script: the reuse
-    calls are the dispatch runs that start at a rotary-table dispatch and hold a probe
+    calls are the dispatch runs that start at a set-up dispatch and hold a probe
     selection; one call's table, then each kernel class averaged over the last n_last calls
     (the timed steps of a run with --steps n_last)."""
     import collections
@@ -168,12 +170,12 @@ def trace_summary(path, n_last):
     rows = sorted(csv.DictReader(open(path)), key=lambda r: int(r["Start_Timestamp"]))
 
     def short(n):
-        return re.sub(r"\(.*\)$", "", n).replace("void ", "")
+        return re.sub(r"\(.*\)$", "", n.replace("(anonymous namespace)::", "")).replace("void ", "")
 
     def dur(r):
         return (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
 
-    starts = [i for i, r in enumerate(rows) if "k_rope_table" in r["Kernel_Name"]]
+    starts = [i for i, r in enumerate(rows) if "k_setup" in r["Kernel_Name"]]
     segs = [rows[a:b] for a, b in zip(starts, starts[1:] + [len(rows)])]
     reuse = [sg for sg in segs if any("k_select_rank" in r["Kernel_Name"] for r in sg)]
     last = reuse[-n_last:]
