@@ -904,21 +904,58 @@ __global__ __launch_bounds__(512) void k_attn_f32(const float *__restrict__ Q, c
     s_l[wave][lr] = l;
   }
   __syncthreads();
-  for (int x = threadIdx.x; x < 16 * HD; x += 512) {
-    const int i = x / HD, d = x - i * HD;
-    if (row0 + i >= R) break;
+  for (int i = wave; i < 16 && row0 + i < R; i += NW) {  // a wave per row, a lane per dim (or two)
     float mm = s_m[0][i];
 #pragma unroll
     for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_m[w][i]);
-    float so = 0.f, sl = 0.f;
+    float so[HD / 64] = {}, sl = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       if (s_m[w][i] == -INFINITY) continue;  // no key of the row in this wave's tiles
       const float a = __builtin_amdgcn_exp2f(s_m[w][i] - mm);
-      so = fmaf(a, s_o[w][d][i], so);
+#pragma unroll
+      for (int c = 0; c < HD / 64; ++c) so[c] = fmaf(a, s_o[w][64 * c + lane][i], so[c]);
       sl = fmaf(a, s_l[w][i], sl);
     }
-    out[((size_t)(row0 + i) * hq + head) * HD + d] = so / sl;
+    bool nan = false;
+#pragma unroll
+    for (int c = 0; c < HD / 64; ++c) nan |= so[c] != so[c];
+    if (__ballot(nan && sl == sl) != 0) {
+      // NaN over a sum that is none: an infinite or NaN value. It may be that of a key which
+      // another row of the block sees and this one does not (its p of 0 makes NaN of it too),
+      // so the row is formed again over its own keys, a lane per key for the scores.
+      const int end = __shfl(lim, i, 64);
+      const float *q = Q + ((size_t)(row0 + i) * hq + head) * HD;
+      float rm = -INFINITY;
+      sl = 0.f;
+#pragma unroll
+      for (int c = 0; c < HD / 64; ++c) so[c] = 0.f;
+      for (int k0 = 0; k0 <= end; k0 += 64) {
+        const float *k = Kc + ((size_t)min(k0 + lane, end) * hkv + kvh) * HD;
+        f32x4_t s4 = zero;
+        for (int d = 0; d < HD; d += 4)
+          s4 += *reinterpret_cast<const f32x4_t *>(q + d) *
+                *reinterpret_cast<const f32x4_t *>(k + d);
+        const float sum = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+        const float s = k0 + lane <= end ? sum * scale_log2 : -INFINITY;
+        const float m_new = fmaxf(rm, wave_max(s)), off = m_new == -INFINITY ? 0.f : m_new;
+        const float p = __builtin_amdgcn_exp2f(s - off);
+        const float alpha = __builtin_amdgcn_exp2f(rm - off);
+        rm = m_new;
+        sl = sl * alpha + wave_sum(p);
+#pragma unroll
+        for (int c = 0; c < HD / 64; ++c) so[c] *= alpha;
+        for (int e = 0; e < 64 && k0 + e <= end; ++e) {
+          const float pe = __shfl(p, e, 64);
+          const float *v = Vc + ((size_t)(k0 + e) * hkv + kvh) * HD + lane;
+#pragma unroll
+          for (int c = 0; c < HD / 64; ++c) so[c] = fmaf(pe, v[64 * c], so[c]);
+        }
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < HD / 64; ++c)
+      out[((size_t)(row0 + i) * hq + head) * HD + 64 * c + lane] = so[c] / sl;
   }
 }
 

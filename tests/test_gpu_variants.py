@@ -162,6 +162,41 @@ def test_fp32_attention(hq, hkv, hd, rows, n_keys):
     assert max_rel(f64(out), ref) < 1e-5
 
 
+def _attention_visible_only(q, pos, k, v):
+    """The oracle's attention, each row over no other keys than those it may see."""
+    with np.errstate(invalid="ignore"):
+        return np.concatenate([oracle.attention(q[i:i + 1], pos[i:i + 1], k[:p + 1], v[:p + 1],
+                                                np.arange(p + 1)) for i, p in enumerate(pos)]
+                              ).reshape(len(pos), -1)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("hd,pos,key", [
+    (64, np.arange(40), 18),    # inside a 16-row block: rows 16 and 17 may not see it
+    (128, np.arange(40), 39),   # the last key of the last block, which masked keys re-read
+    (64, np.arange(0, 300, 9), 142), (128, np.array([3, 4, 5, 290]), 6),
+    (64, np.array([130, 131, 132]), 131)])
+def test_fp32_attention_hidden_values_stay_hidden(hd, pos, key, bad):
+    """An infinite or NaN value reaches the rows that see its key and no other: the rows before
+    it stay exact, those after it hold what the plain sums give."""
+    pos = pos.astype(np.int32)
+    rows, n_keys = len(pos), 300
+    q, k, v = (synthetic.random_array((n, h, hd), 60 + i).astype(np.float32)
+               for i, (n, h) in enumerate([(rows, 2), (n_keys, 1), (n_keys, 1)]))
+    v[key, 0, ::3] = bad
+    m = akvs.ModelCfg(1, 64, 2, 1, hd, 64, 16, 1e4, 1e-6, akvs.AKVS_F32)
+    out = torch.empty((rows, 2 * hd), device=DEV)
+    akvs.akvs_sparse_query_attention(to_dev(q), to_dev(pos), rows, to_dev(k), to_dev(v), n_keys, m,
+                                     out)
+    ref = _attention_visible_only(q.astype(np.float64), pos, k.astype(np.float64),
+                                  v.astype(np.float64))
+    got = f64(out)
+    fin = np.isfinite(ref)
+    assert fin[pos < key].all() and not fin[pos >= key].all()
+    assert max_rel(got[fin], ref[fin]) < 1e-5
+    np.testing.assert_array_equal(got[~fin], ref[~fin])
+
+
 @pytest.mark.parametrize("d,hq,hkv,hd,ffn,rows", [
     (2048, 16, 4, 128, 2176, 1), (2048, 16, 4, 128, 2176, 31), (2048, 16, 4, 128, 2176, 33),
     (2048, 16, 4, 128, 2176, 65), (2048, 16, 4, 128, 2176, 97), (2048, 16, 4, 128, 2176, 200),
