@@ -905,17 +905,27 @@ __global__ __launch_bounds__(512) void k_attn_f32(const float *__restrict__ Q, c
   }
   __syncthreads();
   for (int i = wave; i < 16 && row0 + i < R; i += NW) {  // a wave per row, a lane per dim (or two)
-    float mm = s_m[0][i];
+    float mw[NW], lw[NW], mm = -INFINITY;
 #pragma unroll
-    for (int w = 1; w < NW; ++w) mm = fmaxf(mm, s_m[w][i]);
+    for (int w = 0; w < NW; ++w) {
+      mw[w] = s_m[w][i];
+      lw[w] = s_l[w][i];
+    }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) mm = fmaxf(mm, mw[w]);
     float so[HD / 64] = {}, sl = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      if (s_m[w][i] == -INFINITY) continue;  // no key of the row in this wave's tiles
-      const float a = __builtin_amdgcn_exp2f(s_m[w][i] - mm);
+      // a wave without a key of the row has l = 0 (m = -inf is also what NaN scores leave, with
+      // a sum of NaN); selected, not branched around, so that all LDS reads go out together
+      const float a = __builtin_amdgcn_exp2f(mw[w] - mm);
+      const bool none = lw[w] == 0.f;
 #pragma unroll
-      for (int c = 0; c < HD / 64; ++c) so[c] = fmaf(a, s_o[w][64 * c + lane][i], so[c]);
-      sl = fmaf(a, s_l[w][i], sl);
+      for (int c = 0; c < HD / 64; ++c) {
+        const float x = fmaf(a, s_o[w][64 * c + lane][i], so[c]);
+        so[c] = none ? so[c] : x;
+      }
+      sl = none ? sl : fmaf(a, lw[w], sl);
     }
     bool nan = false;
 #pragma unroll

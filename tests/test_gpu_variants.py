@@ -197,6 +197,31 @@ def test_fp32_attention_hidden_values_stay_hidden(hd, pos, key, bad):
     np.testing.assert_array_equal(got[~fin], ref[~fin])
 
 
+@pytest.mark.parametrize("hd,pos,key", [
+    (64, np.arange(40), 16), (128, np.arange(40), 32),    # alone in its wave's share of a row
+    (128, np.arange(0, 300, 3), 144), (64, np.array([127, 128, 129]), 128),
+    (64, np.array([0]), 0)])
+def test_fp32_attention_nan_scores_are_kept(hd, pos, key):
+    """A NaN key makes NaN of every row that sees it, also where it is the only visible key of
+    a wave's tiles, and of no other row."""
+    pos = pos.astype(np.int32)
+    rows, n_keys = len(pos), 300
+    q, k, v = (synthetic.random_array((n, h, hd), 70 + i).astype(np.float32)
+               for i, (n, h) in enumerate([(rows, 2), (n_keys, 1), (n_keys, 1)]))
+    k[key, 0, 5] = np.nan
+    m = akvs.ModelCfg(1, 64, 2, 1, hd, 64, 16, 1e4, 1e-6, akvs.AKVS_F32)
+    out = torch.empty((rows, 2 * hd), device=DEV)
+    akvs.akvs_sparse_query_attention(to_dev(q), to_dev(pos), rows, to_dev(k), to_dev(v), n_keys, m,
+                                     out)
+    got = f64(out)
+    assert np.isnan(got[pos >= key]).all()
+    clean = pos < key
+    if clean.any():
+        ref = _attention_visible_only(q[clean].astype(np.float64), pos[clean],
+                                      k.astype(np.float64), v.astype(np.float64))
+        assert max_rel(got[clean], ref) < 1e-5
+
+
 @pytest.mark.parametrize("d,hq,hkv,hd,ffn,rows", [
     (2048, 16, 4, 128, 2176, 1), (2048, 16, 4, 128, 2176, 31), (2048, 16, 4, 128, 2176, 33),
     (2048, 16, 4, 128, 2176, 65), (2048, 16, 4, 128, 2176, 97), (2048, 16, 4, 128, 2176, 200),
