@@ -697,8 +697,9 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
 // Merge of the key splits of one (row, head): split s holds its output over its own keys,
 // o_s (bf16, normalised by its own sum l_s), and (m_s, l_s); the result is
 // sum_s w_s o_s / sum_s w_s with w_s = 2^(m_s - max m) l_s, added in split order. A split
-// whose keys all lie past the row (causal mask) holds m = -inf and is skipped, never
-// multiplied in (its part_o slot holds whatever the workspace held). With a device-planned
+// whose keys all lie past the row (causal mask) holds m = -inf and l = 0 and is skipped, never
+// multiplied in (its part_o slot holds whatever the workspace held); one of NaN scores holds
+// m = -inf and l = NaN and makes NaN of the row. With a device-planned
 // split a tile may use fewer splits than the launch's count: l = -1 after its last one
 // ends the list (the slots past it are stale); l = -1 in the first slot marks a row whose
 // tile ran as one piece and whose output the attention block wrote itself.
@@ -748,7 +749,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
     const float moff = mx == -INFINITY ? 0.f : mx;
 #pragma unroll
     for (int u = 0; u < MAXS; ++u) {
-      if (u >= n || ml[u].x == -INFINITY) continue;
+      if (u >= n || ml[u].y == 0.f) continue;
       const float w = exp2f(ml[u].x - moff) * ml[u].y;
       l += w;
 #pragma unroll
@@ -766,7 +767,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
     for (int sp = 0; sp < n; ++sp) {
       const size_t pi = sp * stride + item;
       const float2 ml = *reinterpret_cast<const float2 *>(part_ml + 2 * pi);
-      if (ml.x == -INFINITY) continue;  // no visible key: its part_o was never written
+      if (ml.y == 0.f) continue;  // no visible key: its part_o was never written
       float o[8];
       load8(part_o + pi * hd + e0, o);
       const float w = exp2f(ml.x - moff) * ml.y;

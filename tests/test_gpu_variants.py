@@ -222,6 +222,28 @@ def test_fp32_attention_nan_scores_are_kept(hd, pos, key):
         assert max_rel(got[clean], ref) < 1e-5
 
 
+def test_attention_pieces_keep_nan_scores():
+    """bf16 rows whose key range is cut into pieces: a row whose piece holds no other visible key
+    than a NaN one is NaN, wherever the pieces begin."""
+    hq, hkv, hd, n_keys = 4, 1, 128, 4500
+    m = akvs.ModelCfg(1, 64, hq, hkv, hd, 64, 16, 1e4, 1e-6, akvs.AKVS_BF16)
+    keys = np.arange(64, n_keys, 64)
+    q, k, v = (storage_round(synthetic.random_array((n, h, hd), 80 + i), torch.bfloat16)
+               for i, (n, h) in enumerate([(len(keys), hq), (n_keys, hkv), (n_keys, hkv)]))
+    qd, kd, vd, pd = to_dev(q), to_dev(k), to_dev(v), to_dev(keys.astype(np.int32))
+    nbytes = akvs.akvs_attention_workspace_size(m, len(keys), n_keys)
+    assert nbytes > 0
+    ws = torch.zeros(nbytes, dtype=torch.uint8, device=DEV)
+    for i, key in enumerate(keys):
+        saved = kd[key].clone()
+        kd[key, 0, 5] = float("nan")
+        out = torch.empty((len(keys), hq * hd), dtype=torch.bfloat16, device=DEV)
+        akvs.akvs_sparse_query_attention(qd, pd, len(keys), kd, vd, n_keys, m, out, ws)
+        nan = torch.isnan(out).all(dim=1).cpu().numpy()
+        assert nan[i:].all() and not torch.isnan(out[:i]).any()
+        kd[key] = saved
+
+
 @pytest.mark.parametrize("d,hq,hkv,hd,ffn,rows", [
     (2048, 16, 4, 128, 2176, 1), (2048, 16, 4, 128, 2176, 31), (2048, 16, 4, 128, 2176, 33),
     (2048, 16, 4, 128, 2176, 65), (2048, 16, 4, 128, 2176, 97), (2048, 16, 4, 128, 2176, 200),
