@@ -592,6 +592,68 @@ __global__ __launch_bounds__(256, 2) void k_head_rows(const float *__restrict__ 
     step(k0, l0, l1);
     if (k0 + HR_K < D) step(k0 + HR_K, l1, l0);
   }
+  // An infinity or NaN may come from the split itself (inf - inf, 0 * inf): such a value is
+  // formed again from the unsplit row by the whole wave, unless the row holds a NaN and the
+  // value is one by right. A call over 16 rows at 3B width takes 150 us; with a NaN in one row
+  // 154 and with an infinity in one 278 (5856 both with a lane per value), with one in every
+  // row 2206, as the 16 rows one by one.
+  bool odd = false;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int j = 0; j < SUB; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) odd |= !(fabsf(tot[b][j][i]) < INFINITY);
+  if (__builtin_expect(__ballot(odd) != 0, 0)) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll 1
+      for (int x = 0; x < 16; ++x) {  // row 16 b + x of h
+        if (16 * b + x >= rows) break;
+        const float *hr = h + (size_t)(16 * b + x) * D;
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < SUB; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) any |= lr == x && !(fabsf(tot[b][j][i]) < INFINITY);
+        if (__ballot(any) == 0) continue;
+        bool nan = false;
+        for (int k = lane * 8; k < D; k += 512) {
+          float a[8];
+          load8(hr + k, a);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) nan |= a[e] != a[e];
+        }
+        if (__ballot(nan) != 0) continue;
+#pragma unroll
+        for (int j = 0; j < SUB; ++j) {
+          bool mine = false;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) mine |= lr == x && !(fabsf(tot[b][j][i]) < INFINITY);
+          unsigned long long todo = __ballot(mine);
+          while (todo) {  // the four vocabulary rows of lane `at`, together
+            const int at = __ffsll((long long)todo) - 1, n = n0 + 16 * j + 4 * (at >> 4);
+            todo &= todo - 1;
+            float d[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int k = lane * 8; k < D; k += 512) {
+              float a[8], w[4][8];
+              load8(hr + k, a);
+#pragma unroll
+              for (int i = 0; i < 4; ++i) load8(W + (size_t)min(n + i, V - 1) * D + k, w[i]);
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) d[i] = fmaf(w[i][e], a[e], d[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float v = wave_sum(d[i]);
+              if (lane == at && !(fabsf(tot[b][j][i]) < INFINITY)) tot[b][j][i] = v;
+            }
+          }
+        }
+      }
+  }
   __syncthreads();  // every wave is done with its tiles: their LDS holds the waves' picks
   float(*s_val)[16 * NB] = reinterpret_cast<float(*)[16 * NB]>(s_w0);
   int(*s_idx)[16 * NB] = reinterpret_cast<int(*)[16 * NB]>(s_w1);
@@ -609,14 +671,6 @@ __global__ __launch_bounds__(256, 2) void k_head_rows(const float *__restrict__ 
       for (int i = 0; i < 4; ++i) {
         v[i] = tot[b][j][i];
         if (r >= rows || n + i >= V) continue;
-        // an infinity or NaN may come from the split itself (inf - inf, 0 * inf): such a
-        // value is formed from the unsplit row
-        if (!(fabsf(v[i]) < INFINITY)) {
-          float d = 0.f;
-          for (int k = 0; k < D; ++k)
-            d = fmaf(bf2f(W[(size_t)(n + i) * D + k]), h[(size_t)r * D + k], d);
-          v[i] = d;
-        }
         if (better(v[i], n + i, bv, bi)) { bv = v[i]; bi = n + i; }
       }
       if (logits && r < rows) {

@@ -112,6 +112,54 @@ def test_lm_head_rows_infinities_and_nan():
     assert toks[0].item() == 17 and toks[2].item() == -1
 
 
+def _gpu_us(f, reps=5):
+    """Best of a few timings of one call, in us."""
+    f()
+    best = float("inf")
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("fill", [float("nan"), float("inf")])
+def test_lm_head_nonfinite_row_costs_no_other_row(fill):
+    """One row of h that is not finite leaves the call's time of the order of the finite one's
+    (at 3B width a single row's own sums are one read of the vocabulary, as the whole call is),
+    and the other rows' logits as they were."""
+    vocab, d, rows = 128256, 3072, 16
+    sh = synthetic.ModelShape("head", 1, d, 2, 2, 64, 128, vocab, 1e4)
+    m = akvs.model_cfg(sh)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    w = (torch.randn((vocab, d), device=DEV, generator=g) * 0.02).to(torch.bfloat16)
+    h = torch.randn((rows, d), device=DEV, generator=g)
+    bad = h.clone()
+    bad[5, 7] = fill
+    ws = torch.empty(akvs.akvs_decode_workspace_size(m, 0), dtype=torch.uint8, device=DEV)
+    out = {}
+    us = {}
+    for name, x in (("fine", h), ("bad", bad)):
+        logits = torch.empty((rows, vocab), device=DEV)
+        toks = torch.empty(rows, dtype=torch.int32, device=DEV)
+        us[name] = _gpu_us(lambda: akvs.akvs_lm_head(x, rows, w, m, logits, toks, ws))
+        out[name] = (logits, toks)
+    others = torch.arange(rows, device=DEV) != 5
+    for a, b in zip(out["fine"], out["bad"]):
+        assert torch.equal(a[others], b[others])
+    row = out["bad"][0][5]
+    if fill != fill:
+        assert torch.isnan(row).all() and int(out["bad"][1][5]) == -1
+    else:  # h = inf: +-inf by the sign of the weight, NaN where it is 0
+        ref = torch.where(w[:, 7] == 0, float("nan"), torch.sign(w[:, 7].float()) * fill)
+        assert torch.equal(torch.isnan(row), torch.isnan(ref))
+        assert torch.equal(row[~torch.isnan(ref)], ref[~torch.isnan(ref)])
+    assert us["bad"] < 4 * us["fine"], us
+
+
 @pytest.mark.parametrize("d,hq,hkv,hd,ffn,rows", [
     (72, 3, 1, 64, 100, 1), (72, 3, 1, 64, 100, 17), (8, 1, 1, 64, 4, 16),
     (200, 4, 2, 128, 1028, 33), (200, 4, 2, 128, 1028, 2080)])
