@@ -1444,13 +1444,14 @@ akvs_status akvs_lm_head(const float *h, int32_t n_rows, const void *w_out,
   const size_t need = carve_decode(nullptr, m, 1, b);
   REQUIRE(ws && ws_bytes >= need, AKVS_ENOSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
   carve_decode(ws, m, 1, b);
-  // Several rows of a bf16 model go together where their partials fit the one-row layout
-  // (a part_val entry per 8 vocabulary rows), which small vocabularies do not.
+  // Several rows of a bf16 model go together where that is the faster way (head_rows_pay) and
+  // their partials fit the one-row layout (a part_val entry per 8 vocabulary rows).
   int sub, r = 0;
   const int hb = head_rows_blocks(m->vocab, gemm_cu_count(), &sub);
   const int most = std::min(HEAD_ROWS_MAX, gemv_blocks(m->vocab) / hb);
-  while (m->dtype == AKVS_BF16 && most > 1 && n_rows - r > 1) {
+  while (m->dtype == AKVS_BF16) {
     const int n = std::min(most, n_rows - r);
+    if (n < 2 || !head_rows_pay(n, m->vocab, m->d_model)) break;
     LAUNCH(AKVS_K_GEMV,
            launch_head_rows(h + (size_t)r * m->d_model, n, w_out, m->vocab, m->d_model,
                             logits ? logits + (size_t)r * m->vocab : nullptr, b.part_val,

@@ -757,6 +757,18 @@ int head_rows_blocks(int V, int cus, int *sub) {
   return *sub == 5 ? b5 : b4;
 }
 
+// A wave of the several-row kernel walks the whole width, 0.61 us per 64 columns (1.02 with more
+// than 16 rows) and 6 (8) us besides, however few its vocabulary rows; a one-row launch and its
+// pick spread over the chip and take 4.7 us, 0.22 per 1000 vocabulary rows and 0.07 per MB of
+// weights, 0.27 past the 34 MB that the L2s hold. So small vocabularies take a few rows one by
+// one (measured together and one by one: 1000 x 4096, 2 rows 48 and 13.5 us, 4 rows 48 and 24.5;
+// 8000 x 3072, 2 rows 39 and 28; 16000 x 1024, 2 rows 19 and 23; 32000 x 4096, 2 rows 55 and 91).
+bool head_rows_pay(int n, int V, int D) {
+  const double steps = D / 64.0, mb = 2e-6 * V * D;
+  const double one = 4.7 + 0.22e-3 * V + 0.067 * mb + 0.2 * std::max(0.0, mb - 34.0);
+  return (n > 16 ? 8 + 1.02 * steps : 6 + 0.61 * steps) < n * one;
+}
+
 hipError_t launch_head_rows(const float *h, int rows, const void *W, int V, int D, float *logits,
                             float *part_val, int32_t *part_idx, int32_t *tokens, hipStream_t s) {
   if (rows < 1 || rows > HEAD_ROWS_MAX || D % HR_K) return hipErrorInvalidValue;

@@ -220,6 +220,8 @@ hipError_t launch_pick(const float *part_val, const int32_t *part_idx, int n, in
 // rows * head_rows_blocks(V) entries.
 constexpr int HEAD_ROWS_MAX = 32;
 int head_rows_blocks(int V, int cus, int *sub);
+// true where n rows in one launch are estimated faster than n one-row launches
+bool head_rows_pay(int n, int V, int D);
 hipError_t launch_head_rows(const float *h, int rows, const void *W, int V, int D, float *logits,
                             float *part_val, int32_t *part_idx, int32_t *tokens, hipStream_t s);
 

@@ -160,6 +160,30 @@ def test_lm_head_nonfinite_row_costs_no_other_row(fill):
     assert us["bad"] < 4 * us["fine"], us
 
 
+@pytest.mark.parametrize("vocab,d,rows", [(1000, 4096, 2), (512, 5120, 3)])
+def test_lm_head_few_rows_of_small_vocabularies(vocab, d, rows):
+    """A call over a few rows takes no longer than as many calls over one (a block of the
+    several-row kernel walks the whole width, which small vocabularies leave with few blocks)."""
+    sh = synthetic.ModelShape("head", 1, d, 2, 2, 64, 128, vocab, 1e4)
+    m = akvs.model_cfg(sh)
+    w = to_dev(synthetic.random_array((vocab, d), 4) * 0.02, torch.bfloat16)
+    h = to_dev(synthetic.random_array((rows, d), 5).astype(np.float32))
+    ws = torch.empty(akvs.akvs_decode_workspace_size(m, 0), dtype=torch.uint8, device=DEV)
+    logits = torch.empty((rows, vocab), device=DEV)
+    toks = torch.empty(rows, dtype=torch.int32, device=DEV)
+
+    def whole():
+        for _ in range(50):
+            akvs.akvs_lm_head(h, rows, w, m, logits, toks, ws)
+
+    def single():
+        for _ in range(50):
+            for r in range(rows):
+                akvs.akvs_lm_head(h[r:r + 1], 1, w, m, logits[r:r + 1], toks[r:r + 1], ws)
+
+    assert _gpu_us(whole) < 1.4 * _gpu_us(single)
+
+
 @pytest.mark.parametrize("d,hq,hkv,hd,ffn,rows", [
     (72, 3, 1, 64, 100, 1), (72, 3, 1, 64, 100, 17), (8, 1, 1, 64, 4, 16),
     (200, 4, 2, 128, 1028, 33), (200, 4, 2, 128, 1028, 2080)])
