@@ -154,6 +154,17 @@ size_t akvs_step_workspace_size(const akvs_model_cfg *m, int32_t n_rows);
  * call would not split (fp32 models, or enough row tiles to fill the GPU). */
 size_t akvs_attention_workspace_size(const akvs_model_cfg *m, int32_t n_rows, int32_t n_keys);
 
+/* The kernels that akvs_probe_qkv and akvs_probe_out_mlp take for n_rows rows: out (host, [4]) =
+ * codes of the w_qkv, w_o, w_gate_up and w_down products. Host only; lets tests and profiles
+ * say which kernel ran. A code is one of the enum plus: the tile of the MFMA kernel
+ * (0..3: 16 x 64, 32 x 64, 16 x 128, 32 x 128) for AKVS_G_F32_MFMA; 10 x tile + K slices for
+ * AKVS_G_FEW; the tile for AKVS_G_8WAVE; the K slices for AKVS_G_8WAVE_SPLIT. */
+enum {
+  AKVS_G_F32_MFMA = 0, AKVS_G_F32_LDS = 10, AKVS_G_FEW = 100, AKVS_G_8WAVE = 200,
+  AKVS_G_8WAVE_SPLIT = 300, AKVS_G_4WAVE = 400
+};
+akvs_status akvs_projection_kernels(const akvs_model_cfg *m, int32_t n_rows, int32_t *out);
+
 /* ---- step entries ---------------------------------------------------------------- */
 
 /* Rotary table for positions 0..n_pos-1 (Sec. 2: reused states are moved to their new

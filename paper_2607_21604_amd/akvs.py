@@ -20,6 +20,8 @@ LIB_PATH = os.path.join(HERE, "libakvs.so")
 
 AKVS_OK, AKVS_EINVAL, AKVS_ESHAPE, AKVS_EDTYPE, AKVS_EUNSUPPORTED, AKVS_ENOSPACE, AKVS_EHIP = range(7)
 AKVS_F32, AKVS_BF16, AKVS_U4G64, AKVS_U2G64, AKVS_E4M3G64 = range(5)
+AKVS_G_F32_MFMA, AKVS_G_F32_LDS = 0, 10  # akvs_projection_kernels
+AKVS_G_FEW, AKVS_G_8WAVE, AKVS_G_8WAVE_SPLIT, AKVS_G_4WAVE = 100, 200, 300, 400
 AKVS_F_NO_CORRECTION = 1
 AKVS_F_UNIT_WEIGHTS = 2
 AKVS_F_FRESH_IF_RECOMPUTED = 4
@@ -82,6 +84,7 @@ _SIGS = {
     "akvs_workspace_size": (ctypes.c_size_t, [ctypes.POINTER(ModelCfg), ctypes.POINTER(ReuseCfg), _I]),
     "akvs_step_workspace_size": (ctypes.c_size_t, [ctypes.POINTER(ModelCfg), _I]),
     "akvs_attention_workspace_size": (ctypes.c_size_t, [ctypes.POINTER(ModelCfg), _I, _I]),
+    "akvs_projection_kernels": (_I, [ctypes.POINTER(ModelCfg), _I, _P]),
     "akvs_rope_table": (_I, [_I, _I, ctypes.c_float, _P, _P]),
     "akvs_rerotate_keys": (_I, [ctypes.POINTER(Cache), _I, _I, _I, _P, _P, _I, _P, _P, _I, _P]),
     "akvs_check_divergence": (_I, [_P, _P, _I, ctypes.POINTER(Cache), _I, _I, _I, _P, _P, _I, _P,
@@ -240,6 +243,15 @@ def akvs_step_workspace_size(m: ModelCfg, n_rows: int) -> int:
 
 def akvs_attention_workspace_size(m: ModelCfg, n_rows: int, n_keys: int) -> int:
     return load().akvs_attention_workspace_size(ctypes.byref(m), int(n_rows), int(n_keys))
+
+
+def akvs_projection_kernels(m: ModelCfg, n_rows: int):
+    """Codes (G_*) of the kernels that a layer's QKV, output, gate/up and down projections take
+    over n_rows rows."""
+    out = torch.zeros(4, dtype=torch.int32)
+    _check(load().akvs_projection_kernels(ctypes.byref(m), int(n_rows), out.data_ptr()),
+           "akvs_projection_kernels")
+    return tuple(int(x) for x in out)
 
 
 def akvs_rope_table(n_pos, head_dim, theta, table, stream=None):

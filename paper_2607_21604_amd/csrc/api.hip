@@ -730,6 +730,24 @@ size_t akvs_step_workspace_size(const akvs_model_cfg *m, int32_t n_rows) {
   return carve_step(nullptr, m, n_rows, &x, &a, &g);
 }
 
+akvs_status akvs_projection_kernels(const akvs_model_cfg *m, int32_t n_rows, int32_t *out) {
+  akvs_status st = check_model(m);
+  if (st) return st;
+  REQUIRE(n_rows >= 1, AKVS_EINVAL, "n_rows must be >= 1");
+  REQUIRE(out, AKVS_EINVAL, "NULL argument");
+  const int D = m->d_model, F = m->ffn_dim, hqw = m->n_q_heads * m->head_dim;
+  const int qkvw = hqw + 2 * m->n_kv_heads * m->head_dim;
+  float some, *part = layer_gemm_part(m, n_rows) ? &some : nullptr;  // (never read)
+  const Epi qkv = qkv_epi(m, nullptr, nullptr, nullptr, nullptr, 0, 0, nullptr, 1, 0);
+  const Epi res = simple_epi(EPI_RESID, nullptr, D, AKVS_F32);
+  const Epi act = simple_epi(EPI_SWIGLU, nullptr, F, m->dtype);
+  out[0] = gemm_kernel_of(n_rows, qkvw, D, m->dtype, qkv, part);
+  out[1] = gemm_kernel_of(n_rows, D, hqw, m->dtype, res, part);
+  out[2] = gemm_kernel_of(n_rows, F, D, m->dtype, act, part);
+  out[3] = gemm_kernel_of(n_rows, D, F, m->dtype, res, part);
+  return AKVS_OK;
+}
+
 akvs_status akvs_profile_enable(int32_t class_mask) {
   std::lock_guard<std::mutex> lk(g_prof.mu);
   g_prof.mask = (uint32_t)class_mask & ((1u << AKVS_K_NCLASSES) - 1u);

@@ -15,7 +15,7 @@
 // knows it: k_gemm_bf16_pick runs the chosen kernel's blocks). In every kernel the
 // accumulator tile is staged through LDS so the epilogues can pair columns (rotary halves,
 // gate/up) and write coalesced rows. fp32 path (small models): 16- and 32-row tiles on the
-// fp32 MFMA, same epilogues.
+// fp32 MFMA, over many rows an LDS-tiled kernel on the vector unit; same epilogues.
 #include <algorithm>
 #include <type_traits>
 
@@ -1045,21 +1045,134 @@ __global__ __launch_bounds__(512) void k_gemm_f32(const float *__restrict__ A, i
   epilogue_tile<BM, BN, 512>(Cs, LDC, m0, n0, M_eff, N, epi);
 }
 
-// Tile of the fp32 kernel: 64 columns (128 where a head of 128 must stay whole), 16 rows
-// while those make at most four blocks per CU, then 32 (each operand row read half as often).
+// fp32 GEMM over many rows, on the vector unit: 32x128 tile, BK 32, thread = 4 rows x 4 columns,
+// operands staged through LDS. Where the tiles fill the chip several times over, the operand
+// reads count, which the kernel above repeats in each of its waves: 4000 rows of a width-3072
+// model, output projection 1596 us there, 1166 us (65 TFLOP/s) here; gate/up 8346 and 5873.
+constexpr int GF_M = 32, GF_N = 128, GF_K = 32;
+
+__global__ __launch_bounds__(256) void k_gemm_f32_lds(const float *__restrict__ A, int lda,
+                                                  const float *__restrict__ B, int ldb, int M,
+                                                  int N, int K, const int32_t *m_dev, Epi epi) {
+  __shared__ __attribute__((aligned(16))) float smem[GF_M * (GF_N + 4) > GF_K * (GF_M + GF_N + 8)
+                                                        ? GF_M * (GF_N + 4)
+                                                        : GF_K * (GF_M + GF_N + 8)];
+  float *As = smem;                    // [GF_K][GF_M + 4]  (k-major)
+  float *Bs = smem + GF_K * (GF_M + 4);  // [GF_K][GF_N + 4]
+  const int tid = threadIdx.x;
+  int M_eff = M;
+  if (m_dev) M_eff = min(M, *m_dev);
+  const int m0 = blockIdx.y * GF_M;
+  if (m0 >= M_eff) return;
+  const bool swiglu = epi.mode == EPI_SWIGLU;
+  const int n0 = blockIdx.x * (swiglu ? GF_N / 2 : GF_N);
+  const int tr = tid >> 5, tc = tid & 31;  // rows tr*4.., cols tc*4..
+  float acc[4][4] = {};
+  for (int k0 = 0; k0 < K; k0 += GF_K) {
+    __syncthreads();
+    {  // A: 32 rows x 32 k = 256 float4, one per thread
+      const int r = tid >> 3, kc = (tid & 7) * 4;
+      const int gm = m0 + r, gk = k0 + kc;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (gm < M_eff && gk < K) v = *reinterpret_cast<const float4 *>(A + (size_t)gm * lda + gk);
+      As[(kc + 0) * (GF_M + 4) + r] = v.x;
+      As[(kc + 1) * (GF_M + 4) + r] = v.y;
+      As[(kc + 2) * (GF_M + 4) + r] = v.z;
+      As[(kc + 3) * (GF_M + 4) + r] = v.w;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {  // B: 128 rows x 32 k = 1024 float4
+      const int c = tid + 256 * i;
+      const int r = c >> 3, kc = (c & 7) * 4;
+      int gn;
+      bool ok;
+      if (swiglu) {
+        const int oc = n0 + (r & 63);
+        ok = oc < N;
+        gn = (r < 64) ? oc : N + oc;
+      } else {
+        gn = n0 + r;
+        ok = gn < N;
+      }
+      const int gk = k0 + kc;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (ok && gk < K) v = *reinterpret_cast<const float4 *>(B + (size_t)gn * ldb + gk);
+      Bs[(kc + 0) * (GF_N + 4) + r] = v.x;
+      Bs[(kc + 1) * (GF_N + 4) + r] = v.y;
+      Bs[(kc + 2) * (GF_N + 4) + r] = v.z;
+      Bs[(kc + 3) * (GF_N + 4) + r] = v.w;
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (int k = 0; k < GF_K; ++k) {
+      const float4 a = *reinterpret_cast<const float4 *>(As + k * (GF_M + 4) + tr * 4);
+      const float4 b = *reinterpret_cast<const float4 *>(Bs + k * (GF_N + 4) + tc * 4);
+      const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+    }
+  }
+  __syncthreads();
+  float *Cs = smem;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) Cs[(tr * 4 + i) * (GF_N + 4) + tc * 4 + j] = acc[i][j];
+  __syncthreads();
+  epilogue_tile<GF_M, GF_N, 256>(Cs, GF_N + 4, m0, n0, M_eff, N, epi);
+}
+
+// Which fp32 kernel: times in us estimated from the rounds of one block per CU, fitted to timings
+// of both at 16 to 16000 rows of 21 projections with K of 64 to 8192 (error 9 % rms; the pick
+// costs 0.8 % on average against always taking the faster one). The MFMA kernel's tile is 64
+// columns (128 where a head of 128 must stay whole) by 16 rows while those make at most four
+// blocks per CU, else 32 (each operand row read half as often); it costs its rounds times a step
+// of 16 columns of K each. The LDS-tiled one has three blocks resident per CU, so its step time
+// hardly grows up to there. (MFMA and LDS-tiled at 200, 1000 and 4000 rows: width 256 QKV 10 and
+// 23, 15 and 24, 38 and 29 us; width 3072 output 140 and 297, 405 and 324, 1596 and 1166.)
+struct F32Choice {
+  bool lds;
+  int bm, bn;  // tile of the MFMA kernel
+};
+static F32Choice f32_choice(int M, int N, int K, const Epi &epi) {
+  const int cus = gemm_cu_count();
+  const bool swiglu = epi.mode == EPI_SWIGLU;
+  auto blocks = [&](int bm, int bn) {
+    const int bn_out = swiglu ? bn / 2 : bn;
+    return (long long)((N + bn_out - 1) / bn_out) * ((M + bm - 1) / bm);
+  };
+  F32Choice c{false, 16, epi.mode == EPI_QKV && epi.hd == 128 ? 128 : 64};
+  if (blocks(16, c.bn) > 4LL * cus) c.bm = 32;
+  const double rm = (double)((blocks(c.bm, c.bn) + cus - 1) / cus);
+  double rl = (double)((blocks(GF_M, GF_N) + cus - 1) / cus);
+  if (rl == 5) rl = 6;  // (two rounds of three either way)
+  const double step = c.bn == 64 ? (c.bm == 16 ? 0.206 : 0.337) : (c.bm == 16 ? 0.321 : 0.518);
+  const double t_mfma = 6.1 + rm * (K / 16.0 * step + 1.9);
+  const double t_lds = 4.0 + K / 32.0 * std::max(1.96 + 0.47 * rl, 1.03 * rl) + rl;
+  c.lds = t_lds < t_mfma;
+  return c;
+}
+
 static void launch_f32(const float *A, int lda, const float *B, int ldb, int M, int N, int K,
                        const int32_t *m_dev, const Epi &epi, hipStream_t s) {
-  const int bn = epi.mode == EPI_QKV && epi.hd == 128 ? 128 : 64;
-  const int bn_out = epi.mode == EPI_SWIGLU ? bn / 2 : bn;
-  const int gn = (N + bn_out - 1) / bn_out;
-  const bool small = (long long)gn * ((M + 15) / 16) <= 4LL * gemm_cu_count();
-  const dim3 g(gn, small ? (M + 15) / 16 : (M + 31) / 32), b(512);
+  const bool swiglu = epi.mode == EPI_SWIGLU;
+  const F32Choice c = f32_choice(M, N, K, epi);
+  if (c.lds) {
+    const int bn_out = swiglu ? GF_N / 2 : GF_N;
+    hipLaunchKernelGGL(k_gemm_f32_lds, dim3((N + bn_out - 1) / bn_out, (M + GF_M - 1) / GF_M),
+                       dim3(256), 0, s, A, lda, B, ldb, M, N, K, m_dev, epi);
+    return;
+  }
+  const int bn_out = swiglu ? c.bn / 2 : c.bn;
+  const dim3 g((N + bn_out - 1) / bn_out, (M + c.bm - 1) / c.bm), b(512);
 #define AKVS_F32(BM_, BN_)                                                                     \
   hipLaunchKernelGGL((k_gemm_f32<BM_, BN_>), g, b, 0, s, A, lda, B, ldb, M, N, K, m_dev, epi)
-  if (bn == 64) {
-    if (small) AKVS_F32(16, 64); else AKVS_F32(32, 64);
+  if (c.bn == 64) {
+    if (c.bm == 16) AKVS_F32(16, 64); else AKVS_F32(32, 64);
   } else {
-    if (small) AKVS_F32(16, 128); else AKVS_F32(32, 128);
+    if (c.bm == 16) AKVS_F32(16, 128); else AKVS_F32(32, 128);
   }
 #undef AKVS_F32
 }
@@ -1353,6 +1466,22 @@ hipError_t launch_gemm_fixup(const void *, int lda, const void *, int ldb, int M
   hipLaunchKernelGGL((k_gemm_fixup<128, false>), dim3(p.tiles_cap * (128 / G_FR)), dim3(256), 0, s,
                      M, N, K, m_dev, epi, p.n_slots, part);
   return hipGetLastError();
+}
+
+int gemm_kernel_of(int M, int N, int K, int dtype, const Epi &epi, const float *part) {
+  if (M == 0 || N == 0) return -1;
+  if (dtype != AKVS_BF16) {
+    const F32Choice c = f32_choice(M, N, K, epi);
+    return c.lds ? AKVS_G_F32_LDS
+                 : AKVS_G_F32_MFMA + (c.bn == 128 ? 2 : 0) + (c.bm == 32 ? 1 : 0);
+  }
+  const size_t b_rows = epi.mode == EPI_SWIGLU ? 2 * (size_t)N : (size_t)N;
+  if ((size_t)M * K * 2 >= (1u << 31) || b_rows * K * 2 >= (1u << 31)) return AKVS_G_4WAVE;
+  const FewChoice f = few_choice(M, N, K, nullptr, epi, part, 0);
+  if (f.tile >= 0) return AKVS_G_FEW + 10 * f.tile + f.splits;
+  const int sp = part ? w8_k_splits(M, N, K, epi.mode, gemm_cu_count()) : 1;
+  return sp > 1 ? AKVS_G_8WAVE_SPLIT + sp : AKVS_G_8WAVE + gemm_w8_tile(M, N, epi.mode,
+                                                                         gemm_cu_count());
 }
 
 }  // namespace akvs

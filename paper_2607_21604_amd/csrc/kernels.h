@@ -131,6 +131,9 @@ hipError_t launch_gemm_fixup(const void *A, int lda, const void *B, int ldb, int
                              hipStream_t s, float *part = nullptr, int m_min = 0,
                              const NormAfter *norm = nullptr, bool *normed = nullptr);
 size_t gemm_part_floats(int M, int N, int K, int mode);
+// The AKVS_G_* code of the kernel that launch_gemm takes for a row count known on the host (rows
+// of A and B dense).
+int gemm_kernel_of(int M, int N, int K, int dtype, const Epi &epi, const float *part);
 // ---- k_few.hip ----------------------------------------------------------------------
 // The few-row GEMM with tile `tile` of few_tile (k_gemm.hip picks it); splits > 1: RESID only,
 // partials to part [splits][M][N], added to the residual by launch_few_sum.

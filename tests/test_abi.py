@@ -168,6 +168,27 @@ def test_missing_library_fails_loudly(tmp_path, monkeypatch):
         akvs.load(str(tmp_path / "nope.so"))
 
 
+def test_projection_kernels_by_size(lib):
+    """The kernel of each projection of a layer: fp32 products of few rows on the MFMA tiles, of
+    many on the LDS-tiled kernel (25 to 40 % faster there); bf16 ones by row count."""
+    def codes(d, hq, hkv, hd, ffn, rows, dtype):
+        return akvs.akvs_projection_kernels(
+            akvs.ModelCfg(1, d, hq, hkv, hd, ffn, 64, 1e4, 1e-6, dtype), rows)
+
+    f32, bf16 = akvs.AKVS_F32, akvs.AKVS_BF16
+    assert codes(256, 4, 4, 64, 688, 288, f32) == (akvs.AKVS_G_F32_MFMA,) * 4
+    for d, hq, hkv, hd, ffn in ((1024, 16, 4, 64, 2816), (2048, 16, 4, 128, 8192),
+                                (3072, 24, 8, 128, 8192)):
+        assert codes(d, hq, hkv, hd, ffn, 4000, f32) == (akvs.AKVS_G_F32_LDS,) * 4
+        assert all(c < akvs.AKVS_G_F32_LDS for c in codes(d, hq, hkv, hd, ffn, 64, f32))
+    few = codes(3072, 24, 8, 128, 8192, 100, bf16)
+    assert all(akvs.AKVS_G_FEW <= c < akvs.AKVS_G_8WAVE for c in few)
+    many = codes(3072, 24, 8, 128, 8192, 4516, bf16)
+    assert all(akvs.AKVS_G_8WAVE <= c < akvs.AKVS_G_8WAVE_SPLIT for c in many)
+    with pytest.raises(akvs.AkvsError):
+        codes(3072, 24, 8, 128, 8192, 0, bf16)
+
+
 def test_attention_workspace(lib):
     """The key-split workspace of the attention step: sized like the reuse prefill's probe
     layers for a bf16 3B-class head layout, 0 for fp32 models, and a short one refused."""

@@ -184,6 +184,36 @@ def test_lm_head_few_rows_of_small_vocabularies(vocab, d, rows):
     assert _gpu_us(whole) < 1.4 * _gpu_us(single)
 
 
+def _check_projections(shape, rows, tol):
+    """akvs_probe_qkv and akvs_probe_out_mlp against the oracle over sampled rows."""
+    d, hq, hkv, hd = shape.d_model, shape.n_q_heads, shape.n_kv_heads, shape.head_dim
+    dt = synthetic.torch_dtype(shape)
+    w = synthetic.make_weights(shape, seed=rows, std=0.1 if dt == torch.float32 else 0.02,
+                               embed=False)
+    dims = oracle.dims_from(shape)
+    m = akvs.model_cfg(shape)
+    lwd = {k: to_dev(t) for k, t in w["layers"][0].items()}
+    lws = akvs.layer_array({"layers": [lwd]})[0]
+    h = synthetic.random_array((rows, d), 6).astype(np.float32)
+    pos = np.arange(rows, dtype=np.int32)
+    table = torch.empty((rows, hd // 2, 2), device=DEV)
+    akvs.akvs_rope_table(rows, hd, 1e4, table)
+    att = storage_round(synthetic.random_array((rows, hq * hd), 7), dt)
+    ws = torch.full((akvs.akvs_step_workspace_size(m, rows),), 255, dtype=torch.uint8, device=DEV)
+    q = torch.empty((rows, hq, hd), dtype=dt, device=DEV)
+    kf, vf = (torch.empty((rows, hkv, hd), dtype=dt, device=DEV) for _ in range(2))
+    hdev = to_dev(h)
+    akvs.akvs_probe_qkv(hdev, rows, to_dev(pos), m, lws, table, rows, q, kf, vf, ws)
+    akvs.akvs_probe_out_mlp(hdev, rows, to_dev(att), m, lws, ws)
+    some = np.union1d(np.arange(0, rows, 4), np.arange(max(rows - 35, 0), rows))
+    sw = oracle.split_layer(w["layers"][0], dims)
+    h64 = h[some].astype(np.float64)
+    for got, ref in zip((q, kf, vf), oracle.model.project_qkv(h64, pos[some], sw, dims)):
+        assert max_rel(f64(got)[some], ref) < tol
+    ref = oracle.model.output_and_mlp(h64, f64(att)[some], sw, dims)
+    assert max_rel(f64(hdev)[some], ref) < tol
+
+
 @pytest.mark.parametrize("d,hq,hkv,hd,ffn,rows", [
     (72, 3, 1, 64, 100, 1), (72, 3, 1, 64, 100, 17), (8, 1, 1, 64, 4, 16),
     (200, 4, 2, 128, 1028, 33), (200, 4, 2, 128, 1028, 2080)])
@@ -212,6 +242,21 @@ def test_fp32_projections(d, hq, hkv, hd, ffn, rows):
     akvs.akvs_probe_out_mlp(hdev, rows, to_dev(att), m, lws, ws)
     ref = oracle.model.output_and_mlp(h.astype(np.float64), att.astype(np.float64), sw, dims)
     assert max_rel(f64(hdev), ref) < 1e-5
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,ffn,rows,codes", [
+    (1032, 8, 4, 64, 260, 1399, (1, 1, 0, 1)),        # 32 x 64 tiles
+    (264, 24, 8, 128, 260, 897, (3, 0, 0, 0)),        # 32 x 128
+    (200, 4, 2, 128, 1028, 33, (2, 0, 0, 0)),         # 16 x 128
+    (72, 3, 1, 64, 100, 9001, (10, 10, 10, 10)),      # LDS-tiled, K of 72, 192 and 100
+    (264, 5, 1, 64, 260, 6001, (10, 1, 10, 10)),
+    (136, 2, 1, 128, 516, 3009, (10, 0, 10, 0))])
+def test_fp32_projection_kernels(d, hq, hkv, hd, ffn, rows, codes):
+    """Every fp32 tile and the LDS-tiled kernel at remainders of rows, columns and K (a quarter
+    of the rows, the last ones among them, against the oracle)."""
+    shape = synthetic.ModelShape("v", 1, d, hq, hkv, hd, ffn, 64, 1e4, dtype="f32")
+    assert akvs.akvs_projection_kernels(akvs.model_cfg(shape), rows) == codes
+    _check_projections(shape, rows, 1e-5)
 
 
 @pytest.mark.parametrize("hq,hkv,hd,rows,n_keys", [
