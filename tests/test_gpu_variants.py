@@ -437,3 +437,15 @@ def test_correction_finds_the_unit_of_many(dtype, hkv, hd, units):
     mu_k, mu_v, k_corr, v_corr = gpu_offset_and_correction(cs, hkv, hd)
     _, _, rk, rv = oracle_offset_and_correction(cs)
     assert max_rel(f64(k_corr), rk) < 4e-3 and max_rel(f64(v_corr), rv) < 4e-3  # one bf16 rounding
+
+
+@pytest.mark.parametrize("units", [128, 129, 256, 4097, 8193])
+def test_correction_finds_the_unit_in_several_looks(units):
+    """The same with more units than one look tells apart, around the counts where the number of
+    looks and the spacing of their starts change."""
+    rng = np.random.default_rng(units)
+    lens = [int(x) for x in rng.integers(1, 4, size=units)]
+    cs = make_offset_case("bf16", lens, 4, 64, seed=units)
+    mu_k, mu_v, k_corr, v_corr = gpu_offset_and_correction(cs, 4, 64)
+    _, _, rk, rv = oracle_offset_and_correction(cs)
+    assert max_rel(f64(k_corr), rk) < 4e-3 and max_rel(f64(v_corr), rv) < 4e-3  # one bf16 rounding
