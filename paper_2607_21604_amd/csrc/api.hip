@@ -155,7 +155,7 @@ akvs_status check_layers(const akvs_model_cfg *m, const akvs_layer_w *lw) {
 
 struct Meta {
   std::vector<int32_t> m;  // [2][n][4]: key table, value table
-  long long t_ctx = 0, sum_b = 0, sum_b_v = 0, row_cap = 0, row_min = 0, t_all = 0;
+  long long t_ctx = 0, sum_b = 0, sum_b_v = 0, row_cap = 0, row_min = 0, t_all = 0, len_max = 0;
 };
 
 akvs_status check_reuse(const akvs_reuse_cfg *c, int n_layers, Meta *meta) {
@@ -183,7 +183,7 @@ akvs_status check_reuse(const akvs_reuse_cfg *c, int n_layers, Meta *meta) {
   Meta &mt = meta ? *meta : loc;
   const int nc = c->n_chunks;
   mt.m.assign((size_t)nc * 8, 0);
-  long long s = 0, off = 0, off_v = 0, cap = 0, lo = 0;
+  long long s = 0, off = 0, off_v = 0, cap = 0, lo = 0, longest = 0;
   for (int i = 0; i < nc; ++i) {
     const long long n = c->chunk_len[i];
     REQUIRE(n >= 1, AKVS_EINVAL, "chunk %d has length %lld", i, n);
@@ -197,6 +197,7 @@ akvs_status check_reuse(const akvs_reuse_cfg *c, int n_layers, Meta *meta) {
     mv[2] = (int32_t)bv;
     mv[3] = (int32_t)off_v;
     s += n;
+    longest = std::max(longest, n);
     off += b;
     off_v += bv;
     cap += n < b + bv ? n : b + bv;
@@ -210,6 +211,7 @@ akvs_status check_reuse(const akvs_reuse_cfg *c, int n_layers, Meta *meta) {
   mt.row_cap = cap + c->query_len;
   mt.row_min = lo + c->query_len;
   mt.t_all = s + c->query_len;
+  mt.len_max = longest;
   return AKVS_OK;
 }
 
@@ -848,7 +850,8 @@ akvs_status akvs_select_probes(const float *d_k, const float *d_v, const akvs_re
               n_rows && fresh_row,
           AKVS_EINVAL, "NULL argument");
   REQUIRE(aligned16(chunk_meta), AKVS_EINVAL, "chunk_meta misaligned");
-  LAUNCH(AKVS_K_SELECT, launch_select(d_k, d_v, chunk_meta, cfg->n_chunks, (int)mt.t_ctx,
+  LAUNCH(AKVS_K_SELECT, launch_select(d_k, d_v, chunk_meta, cfg->n_chunks, (int)mt.len_max,
+                                      (int)mt.t_ctx,
                                       cfg->query_len, cfg->flags, probe_k, probe_v, w_k, w_v, flags,
                                       chunk_rows, rows, n_rows, fresh_row, stream));
   return AKVS_OK;
@@ -1140,7 +1143,8 @@ akvs_status akvs_reuse_prefill(const int32_t *tokens, const void *embed, const a
            launch_divergence(b.k_chk, b.v_chk, m->dtype, cache_layer(cache, c, Tc, hkv, hd), Tc,
                              hkv, hd, b.tok_delta, b.rope, T, b.d_k, b.d_v, stream));
   }
-  LAUNCH(AKVS_K_SELECT, launch_select(b.d_k, b.d_v, b.meta, nch, Tc, cfg->query_len, cfg->flags,
+  LAUNCH(AKVS_K_SELECT, launch_select(b.d_k, b.d_v, b.meta, nch, (int)mt.len_max, Tc,
+                                      cfg->query_len, cfg->flags,
                                       b.probe_k, b.probe_v, b.w_k, b.w_v, b.flags, b.chunk_rows,
                                       b.rows, b.n_rows, b.fresh_row, stream));
   LAUNCH(AKVS_K_OTHER, launch_gather_rows(b.h_full, T, b.rows, cap, b.n_rows, D, b.h_probe,
@@ -1290,7 +1294,8 @@ akvs_status akvs_reuse_prefill_batch(const int32_t *const *tokens, int32_t batch
              launch_divergence(b.k_chk, b.v_chk, m->dtype, cache_layer(&caches[i], c, Tc, hkv, hd),
                                Tc, hkv, hd, r.tok_delta, b.rope, T_max, r.d_k, r.d_v, stream));
     }
-    LAUNCH(AKVS_K_SELECT, launch_select(r.d_k, r.d_v, r.meta, nch, Tc, cf.query_len, cf.flags,
+    LAUNCH(AKVS_K_SELECT, launch_select(r.d_k, r.d_v, r.meta, nch, (int)mt.len_max, Tc,
+                                        cf.query_len, cf.flags,
                                         r.probe_k, r.probe_v, r.w_k, r.w_v, r.flags, r.chunk_rows,
                                         r.rows, b.n_rows + i, r.fresh_row, stream));
   }

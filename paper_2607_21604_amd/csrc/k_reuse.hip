@@ -1,5 +1,7 @@
 // Reuse-specific kernels: check-layer divergence, probe selection, per-unit offsets,
 // the fused re-rotation + dequantisation + weighted correction, and the cache quantiser.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace akvs {
@@ -109,7 +111,9 @@ hipError_t launch_divergence(const void *k_fresh, const void *v_fresh, int fresh
 // A unit of n tokens makes n^2 comparisons on one block, so what counts is the length of each
 // thread's chain of them: four lanes share a token, each taking four of every sixteen t (one
 // 16-byte LDS read per side), and their counts are added inside the quad. 80 units of 200
-// tokens: 17.4 us with one thread per token, 8.5 us here.
+// tokens: 17.4 us with one thread per token, 8.5 us here. The block has the threads that the
+// longest unit needs, at most 1024: 2000 units of 8 tokens took 24 us in blocks of 1024, 15 us
+// in blocks of one wave (16.5 in blocks of 256 with a thread per token).
 constexpr int SEL_TILE = 1024, SEL_THREADS = 1024, SEL_LANES = 4;
 
 __device__ __forceinline__ int quad_sum(int x) {
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_rank(
   const bool given = (flags & AKVS_F_GIVEN_PROBES) != 0;
   const bool unit_w = (flags & AKVS_F_UNIT_WEIGHTS) != 0;
   const int part = threadIdx.x & (SEL_LANES - 1);
-  for (int jb = 0; jb < n; jb += SEL_THREADS / SEL_LANES) {
+  for (int jb = 0; jb < n; jb += (int)blockDim.x / SEL_LANES) {
     const int j = jb + (int)threadIdx.x / SEL_LANES;
     const bool valid = j < n;
     float dk = (valid && bany > 0) ? d_k[s0 + j] : 0.f;
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_rank(
       for (int tb = 0; tb < n; tb += SEL_TILE) {
         const int tn = min(SEL_TILE, n - tb), tn16 = (tn + 15) & ~15;
         __syncthreads();
-        for (int t = threadIdx.x; t < tn16; t += SEL_THREADS) {
+        for (int t = threadIdx.x; t < tn16; t += blockDim.x) {
           // (fill past the unit's end: below or equal to any value, at a later position)
           const float a = t < tn ? d_k[s0 + tb + t] : -INFINITY;
           const float bv = t < tn ? d_v[s0 + tb + t] : -INFINITY;
@@ -247,12 +251,13 @@ __global__ void k_select_rows(const int4 *meta, int n_chunks, int t_ctx, int q,
 }
 
 hipError_t launch_select(const float *d_k, const float *d_v, const int32_t *meta, int n_chunks,
-                         int t_ctx, int q, uint32_t flags, int32_t *probe_k, int32_t *probe_v,
+                         int len_max, int t_ctx, int q, uint32_t flags, int32_t *probe_k, int32_t *probe_v,
                          float *w_k, float *w_v, uint8_t *tok_flags, int32_t *chunk_rows,
                          int32_t *rows, int32_t *n_rows, int32_t *fresh_row, hipStream_t s) {
   const int4 *m4 = reinterpret_cast<const int4 *>(meta);
-  hipLaunchKernelGGL(k_select_rank, dim3(n_chunks), dim3(SEL_THREADS), 0, s, d_k, d_v, m4, n_chunks, flags,
-                     probe_k, probe_v, w_k, w_v, tok_flags, chunk_rows);
+  const int threads = std::min(SEL_THREADS, (std::min(len_max, SEL_THREADS) * SEL_LANES + 63) & ~63);
+  hipLaunchKernelGGL(k_select_rank, dim3(n_chunks), dim3(threads), 0, s, d_k, d_v, m4, n_chunks,
+                     flags, probe_k, probe_v, w_k, w_v, tok_flags, chunk_rows);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_select_rows, dim3(n_chunks + 1), dim3(64), 0, s, m4, n_chunks, t_ctx, q,

@@ -60,7 +60,7 @@ hipError_t launch_divergence(const void *k_fresh, const void *v_fresh, int fresh
                              const int32_t *tok_delta, const float *rope, int rope_rows,
                              float *d_k, float *d_v, hipStream_t s);
 hipError_t launch_select(const float *d_k, const float *d_v, const int32_t *meta, int n_chunks,
-                         int t_ctx, int q, uint32_t flags, int32_t *probe_k, int32_t *probe_v,
+                         int len_max, int t_ctx, int q, uint32_t flags, int32_t *probe_k, int32_t *probe_v,
                          float *w_k, float *w_v, uint8_t *tok_flags, int32_t *chunk_rows,
                          int32_t *rows, int32_t *n_rows, int32_t *fresh_row, hipStream_t s);
 hipError_t launch_chunk_offset(const void *k_fresh, const void *v_fresh, int fresh_dtype,

@@ -10,7 +10,7 @@ import oracle
 import synthetic
 from paper_2607_21604_amd import akvs
 from tests.test_gpu_steps import (gpu_offset_and_correction, make_offset_case,
-                                  oracle_offset_and_correction)
+                                  oracle_offset_and_correction, run_select)
 from tests.gpu_util import DEV, f64, max_rel, storage_round, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -449,3 +449,23 @@ def test_correction_finds_the_unit_in_several_looks(units):
     mu_k, mu_v, k_corr, v_corr = gpu_offset_and_correction(cs, 4, 64)
     _, _, rk, rv = oracle_offset_and_correction(cs)
     assert max_rel(f64(k_corr), rk) < 4e-3 and max_rel(f64(v_corr), rv) < 4e-3  # one bf16 rounding
+
+
+@pytest.mark.parametrize("longest", [1, 15, 16, 17, 31, 100, 255, 256, 257])
+def test_selection_block_sizes(longest):
+    """Probe lists and recomputed rows bit exact where the longest unit sets the block's threads
+    (one to sixteen waves of 16 tokens each), with shorter units beside it and many ties."""
+    rng = np.random.default_rng(longest)
+    lens = [longest, 1] + [int(x) for x in rng.integers(1, longest + 1, size=40)]
+    tc, q, refresh = sum(lens), 3, (3, 10)
+    d_k = rng.integers(0, 5, size=tc).astype(np.float32) * 0.25
+    d_v = rng.random(tc).astype(np.float32) * 3
+    got, sum_b, _ = run_select(d_k, d_v, lens, q, refresh)
+    keep = np.zeros(tc, bool)
+    for side, d in (("probe_k", d_k), ("probe_v", d_v)):
+        ref = np.concatenate([oracle.select_top(d[s:s + n], oracle.probe_budget(n, *refresh)) + s
+                              for s, n in zip(oracle.chunk_starts(lens), lens)])
+        np.testing.assert_array_equal(got[side][:sum_b], ref)
+        keep[ref] = True
+    rows = np.concatenate([np.nonzero(keep)[0], np.arange(tc, tc + q)])
+    np.testing.assert_array_equal(got["rows"][:int(got["n_rows"][0])], rows)
