@@ -74,14 +74,21 @@ static inline bool attn_whole(int rows, int n_keys) {
 // 51 / 65 / 70 / 87 -> 37 / 49 / 54 / 78 us, 32B heads 62 / 81 / 87 / 145 -> 38 / 52 / 61 / 101;
 // 400 rows over 2500 and 5000 keys, 3B 36 and 48 -> 33 and 41; 159 rows over 1000 keys 23 -> 21.
 // (16 pieces at 250 rows of the 32B heads, or under 2500 keys, cost 2 to 5 % more than 8.)
+// Between 4096 and 6144 keys both are a matter of how full the chip is (timed at 4200 to 7000 keys,
+// five head counts, 1 to 192 rows): 17 to 128 rows are packed there only where the heads one by
+// one would make more than two rounds of blocks (64 rows over 5000 keys, 40 query heads: 35.7
+// -> 35.0 us packed, but 24 heads 29.9 -> 32.1), and more than 128 rows take 16 pieces only
+// where 8 leave compute units idle (159 rows over 4500 keys: 24 heads 32.3 us with 8, 34.9 with
+// 16; 14 heads of 64 26.9 and 25.6).
 struct AttnEqShape {
   int rb, budget, max_pc;
   bool use;
   int pack;  // query heads listed together: 1, or G
 };
 constexpr int kAttnMaxPieces = 8, kAttnFewPieces = 16;  // the merge's all-at-once path
+constexpr int kAttnLongKeys = 4096, kAttnVeryLongKeys = 6144;
 static inline int attn_max_pieces(int rows, int n_keys) {
-  return rows <= 192 && n_keys > 4096 ? kAttnFewPieces : kAttnMaxPieces;
+  return rows <= 192 && n_keys > kAttnLongKeys ? kAttnFewPieces : kAttnMaxPieces;
 }
 
 // rb and budget for `rows` rows (or pairs) of `lists` row lists; false where the tiles fill
@@ -112,7 +119,9 @@ static inline AttnEqShape attn_eq_shape(int rows, int hq, int hkv, int n_keys, i
   if (!attn_eq_blocks(rows, hq, cus, &e.rb, &e.budget)) return e;
   const int G = hq / hkv;
   int rb, budget;
-  if (G > 1 && (rows > 128 || n_keys > 4096) &&
+  const bool packs = rows > 128 || n_keys > kAttnVeryLongKeys ||
+                     (n_keys > kAttnLongKeys && (rows <= 16 || kAttnFewPieces * hq > 2 * cus));
+  if (G > 1 && packs &&
       attn_eq_blocks((long long)rows * G, hkv, cus, &rb, &budget)) {
     const long long single = (long long)((rows + e.rb - 1) / e.rb) * e.rb * hq;
     const long long packed = ((long long)rows * G + rb - 1) / rb * rb * hkv;
@@ -122,7 +131,12 @@ static inline AttnEqShape attn_eq_shape(int rows, int hq, int hkv, int n_keys, i
       e.pack = G;
     }
   }
-  e.max_pc = (int)std::min<long long>(attn_max_pieces(rows, n_keys), part_rows / rows);
+  int most = attn_max_pieces(rows, n_keys);
+  if (rows > 128 && n_keys <= kAttnVeryLongKeys) {
+    const long long tiles = ((long long)rows * e.pack + e.rb - 1) / e.rb * (hq / e.pack);
+    if (tiles * kAttnMaxPieces >= cus) most = kAttnMaxPieces;
+  }
+  e.max_pc = (int)std::min<long long>(most, part_rows / rows);
   e.use = e.max_pc >= 2;
   return e;
 }

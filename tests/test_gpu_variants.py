@@ -403,7 +403,8 @@ def test_few_row_projections(d, hq, hkv, hd, ffn, rows):
 @pytest.mark.parametrize("hq,hkv,hd,rows,n_keys", [
     (10, 2, 128, 33, 4500), (14, 2, 128, 57, 5261), (40, 8, 128, 159, 1100), (3, 1, 64, 9, 4900),
     (24, 8, 128, 1, 4300), (10, 2, 64, 200, 1700), (10, 2, 64, 192, 4097), (16, 1, 128, 193, 4100),
-    (16, 1, 128, 129, 1024), (14, 2, 128, 128, 1000),
+    (16, 1, 128, 129, 1024), (14, 2, 128, 128, 1000), (8, 2, 128, 16, 4097), (8, 2, 128, 17, 4097),
+    (10, 2, 128, 17, 6145), (14, 2, 64, 128, 6144), (14, 2, 64, 64, 6200),
     (4, 2, 128, 203, 203), (4, 2, 64, 384, 768), (4, 2, 128, 385, 769), (4, 4, 128, 20, 384),
     (4, 4, 128, 20, 385)])
 def test_attention_packed_heads_and_short_contexts(hq, hkv, hd, rows, n_keys):
