@@ -143,7 +143,9 @@ static inline AttnEqShape attn_eq_shape(int rows, int hq, int hkv, int n_keys, i
 
 // The plan (one wave): tile t of rb rows sees kt_t = ceil(keys_t / 64) key tiles, keys_t
 // its last row's position + 1. It is cut into c_t = ceil(kt_t / L) ranges of nearly equal
-// length, L the smallest with sum_t c_t <= max(tiles, budget) and c_t <= max_pc. Items
+// length, L >= 2 the smallest with sum_t c_t <= max(tiles, budget) and c_t <= max_pc. (A piece of
+// one key tile costs more than it saves: 159 rows of 40 / 8 heads over 512 keys 21.5 us unpacked,
+// 22.9 packed in pieces of one tile, 19.4 of two; 250 rows of 32 / 8 heads 0.84x with two.) Items
 // (tile, range) are numbered by the tile's range length, longest first (equal lengths:
 // later tile first), a tile's ranges together. plan[0] = {tiles, items, max_t c_t},
 // plan[1 + t] = {c_t, first item of tile t, kt_t} (c_t = 0 past the last tile).
@@ -171,7 +173,7 @@ __global__ __launch_bounds__(64) void k_attn_plan(PlanArgs p0, PlanArgs p1, int 
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) ktmax = max(ktmax, __shfl_xor(ktmax, o, 64));
   const int B = max(nt, budget);
-  int lo = max(1, (ktmax + max_pc - 1) / max_pc), hi = max(lo, ktmax);
+  int lo = max(2, (ktmax + max_pc - 1) / max_pc), hi = max(lo, ktmax);
   while (lo < hi) {  // the same bounds in every lane
     const int L = (lo + hi) >> 1;
     int c = lane < nt ? (kt + L - 1) / L : 0;
