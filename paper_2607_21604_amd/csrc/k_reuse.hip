@@ -861,8 +861,9 @@ __global__ __launch_bounds__(256) void k_quantize(const TX *__restrict__ x, long
   }
 }
 
-// The same for operands that are not aligned for k_quantize's loads and stores: one wave per
-// (row, group of 64); lane = element.
+// The same with one wave per (row, group of 64); lane = element: for operands that are not aligned
+// for k_quantize's loads and stores, and for few groups, which k_quantize leaves on few
+// threads (64 elements each, in turn).
 template <typename TX>
 __global__ void k_quantize_any(const TX *x, int n_rows, int hd, int bits, uint8_t *codes,
                                _Float16 *meta) {
@@ -926,8 +927,12 @@ hipError_t launch_quantize(const void *x, int x_dtype, int n_rows, int hd, int b
                            uint8_t *codes, _Float16 *meta, hipStream_t s) {
   const long long waves = (long long)n_rows * (hd / 64);
   if (waves == 0) return hipSuccess;
-  // rows and groups are dense: octet o holds elements 8o..8o+7 and codes byte o * bits on
-  const bool wide = (reinterpret_cast<uintptr_t>(x) & 15u) == 0 &&
+  // rows and groups are dense: octet o holds elements 8o..8o+7 and codes byte o * bits on.
+  // Groups from which k_quantize is the faster one (bf16, k_quantize and k_quantize_any: 4 bits,
+  // 2000 groups 4.3 and 3.9 us, 8000 4.5 and 5.0; 8 bits, whose codes take three times the
+  // arithmetic, 8000 6.0 and 4.4, 32000 6.2 and 8.6).
+  const bool many = waves > (bits == 8 ? 16384 : 4096);
+  const bool wide = many && (reinterpret_cast<uintptr_t>(x) & 15u) == 0 &&
                     (reinterpret_cast<uintptr_t>(codes) & 7u) == 0 &&
                     (reinterpret_cast<uintptr_t>(meta) & 3u) == 0;
   if (wide) {

@@ -41,10 +41,12 @@ def _near_ties(rows, hd, bits, seed):
 
 
 @pytest.mark.parametrize("bits", [2, 4, 8])
-@pytest.mark.parametrize("rows,hd", [(1, 64), (33, 192), (127, 128), (257, 64)])
+@pytest.mark.parametrize("rows,hd", [(1, 64), (33, 192), (127, 128), (257, 64), (4097, 64),
+                                     (8193, 128), (5462, 192)])
 def test_quantise_codes_at_ties(bits, rows, hd):
     """Bit-exact codes and metadata at the rounding boundaries, for block remainders, fp32 and
-    bf16 inputs, and operands that miss the wide kernel's alignment."""
+    bf16 inputs, operands that miss the wide kernel's alignment, and group counts on both sides
+    of those from which it is taken (4096, or 16384 at 8 bits)."""
     x32 = torch.from_numpy(_near_ties(rows, hd, bits, 7 * rows + bits))
     for x in (x32, x32.to(torch.bfloat16)):
         if bits == 8:
