@@ -257,7 +257,8 @@ akvs_status akvs_apply_correction(const akvs_cache *cache, const float *mu_k, co
  * out: [n_rows][Hq*hd]; all model dtype. positions must be ascending. ws (may be NULL)
  * of ws_bytes >= akvs_attention_workspace_size lets the call split the key range and
  * merge the parts, as the reuse prefill does; a non-NULL ws that is too small is
- * AKVS_ENOSPACE. */
+ * AKVS_ENOSPACE. (Few rows over many keys run with 8 parts a tile in a smaller ws, as the
+ * reuse calls do in theirs.) */
 akvs_status akvs_sparse_query_attention(const void *q, const int32_t *positions, int32_t n_rows,
                                         const void *k, const void *v, int32_t n_keys,
                                         const akvs_model_cfg *m, void *out, void *ws,

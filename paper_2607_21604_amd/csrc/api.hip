@@ -294,9 +294,9 @@ struct AttnUse {
 
 // rows: the largest row count a layer pass uses; uses: the (rows, keys) of its attention
 // calls, which are also the row counts of its projections (sizing the GEMM K-split
-// partials and the attention key-split partials of bf16 models).
+// partials and the attention key-split partials of bf16 models; lean: see attn_part_splits).
 void carve_layer_bufs(Carver &cv, const akvs_model_cfg *m, long long rows,
-                      const std::vector<AttnUse> &uses, LayerBufs &b) {
+                      const std::vector<AttnUse> &uses, LayerBufs &b, bool lean = false) {
   const size_t es = es_of(m->dtype);
   b.x = cv.take<char>((size_t)rows * m->d_model * es);
   b.q = cv.take<char>((size_t)rows * m->n_q_heads * m->head_dim * es);
@@ -313,7 +313,7 @@ void carve_layer_bufs(Carver &cv, const akvs_model_cfg *m, long long rows,
     g = std::max(g, layer_gemm_part(m, u.rows));
     if (m->dtype != AKVS_BF16 || u.rows <= 0) continue;
     const long long sp = attn_part_splits((int)u.rows, m->n_q_heads, m->n_kv_heads, m->head_dim,
-                                          (int)u.n_keys);
+                                          (int)u.n_keys, lean);
     if (sp > 1 && sp * u.rows > worst) worst = sp * u.rows;
   }
   if (g) b.gpart = cv.take<float>(g);
@@ -342,7 +342,7 @@ struct ReuseBufs {
 };
 
 size_t carve_reuse(void *ws, const akvs_model_cfg *m, const akvs_reuse_cfg *c, const Meta &mt,
-                   ReuseBufs &b) {
+                   ReuseBufs &b, bool lean = false) {
   Carver cv(ws);
   const size_t es = es_of(m->dtype);
   const long long T = mt.t_all, Tc = mt.t_ctx, cap = mt.row_cap;
@@ -352,7 +352,7 @@ size_t carve_reuse(void *ws, const akvs_model_cfg *m, const akvs_reuse_cfg *c, c
   b.tok_delta = cv.take<int32_t>((size_t)Tc);
   b.tok_chunk = cv.take<int32_t>((size_t)Tc);
   b.h_full = cv.take<float>((size_t)T * m->d_model);
-  carve_layer_bufs(cv, m, T, {{T, T}, {cap, T}, {c->query_len, T}}, b.lb);
+  carve_layer_bufs(cv, m, T, {{T, T}, {cap, T}, {c->query_len, T}}, b.lb, lean);
   b.k_chk = cv.take<char>((size_t)Tc * kvw * es);
   b.v_chk = cv.take<char>((size_t)Tc * kvw * es);
   b.d_k = cv.take<float>((size_t)Tc);
@@ -577,7 +577,7 @@ struct BatchPlan {
 };
 
 size_t carve_batch(void *ws, const akvs_model_cfg *m, const akvs_reuse_cfg *cfgs, int B,
-                   const BatchPlan &pl, BatchBufs &b) {
+                   const BatchPlan &pl, BatchBufs &b, bool lean = false) {
   Carver cv(ws);
   const size_t es = es_of(m->dtype);
   const int kvw = m->n_kv_heads * m->head_dim, hqw = m->n_q_heads * m->head_dim;
@@ -614,7 +614,7 @@ size_t carve_batch(void *ws, const akvs_model_cfg *m, const akvs_reuse_cfg *cfgs
     for (int i = 0; i < B; ++i) {
       for (long long r : {pl.mt[i].row_cap, (long long)cfgs[i].query_len}) {
         const long long sp = attn_part_splits((int)r, m->n_q_heads, m->n_kv_heads, m->head_dim,
-                                              (int)pl.mt[i].t_all);
+                                              (int)pl.mt[i].t_all, lean);
         if (sp > 1 && sp * r > worst) worst = sp * r;
       }
     }
@@ -940,11 +940,11 @@ akvs_status akvs_apply_correction(const akvs_cache *cache, const float *mu_k, co
 
 // Key-split partials of one attention call over `rows` rows (bf16 models that split).
 static size_t attention_part_floats(const akvs_model_cfg *m, long long rows, long long n_keys,
-                                    size_t *ml_floats) {
+                                    size_t *ml_floats, bool lean = false) {
   *ml_floats = 0;
   if (m->dtype != AKVS_BF16 || rows <= 0) return 0;
   const long long sp =
-      attn_part_splits((int)rows, m->n_q_heads, m->n_kv_heads, m->head_dim, (int)n_keys);
+      attn_part_splits((int)rows, m->n_q_heads, m->n_kv_heads, m->head_dim, (int)n_keys, lean);
   if (sp < 2) return 0;
   *ml_floats = (size_t)(sp * rows) * m->n_q_heads * 2;
   return (size_t)(sp * rows) * m->n_q_heads * m->head_dim / 2;  // bf16 outputs, two per float
@@ -952,8 +952,8 @@ static size_t attention_part_floats(const akvs_model_cfg *m, long long rows, lon
 
 // The split partials, then the plan of the split (launch_attention_plan).
 static size_t attention_ws_bytes(const akvs_model_cfg *m, long long rows, long long n_keys,
-                                 size_t *o_floats, size_t *ml_floats) {
-  *o_floats = attention_part_floats(m, rows, n_keys, ml_floats);
+                                 size_t *o_floats, size_t *ml_floats, bool lean = false) {
+  *o_floats = attention_part_floats(m, rows, n_keys, ml_floats, lean);
   if (!*o_floats) return 0;
   return align256(*o_floats * sizeof(float)) + align256(*ml_floats * sizeof(float)) +
          align256(kAttnPlanInts * sizeof(int32_t));
@@ -980,7 +980,8 @@ akvs_status akvs_sparse_query_attention(const void *q, const int32_t *positions,
   long long part_rows = 0;
   if (ws) {
     size_t o, ml;
-    const size_t need = attention_ws_bytes(m, n_rows, n_keys, &o, &ml);
+    size_t need = attention_ws_bytes(m, n_rows, n_keys, &o, &ml);
+    if (ws_bytes < need) need = attention_ws_bytes(m, n_rows, n_keys, &o, &ml, true);
     REQUIRE(ws_bytes >= need, AKVS_ENOSPACE, "workspace %zu bytes, need %zu", ws_bytes, need);
     if (o) {
       Carver cv(ws);
@@ -1093,9 +1094,10 @@ akvs_status akvs_reuse_prefill(const int32_t *tokens, const void *embed, const a
   REQUIRE(!given || (out->probe_k && out->probe_v), AKVS_EINVAL,
           "AKVS_F_GIVEN_PROBES needs out->probe_k and out->probe_v holding the sets");
   ReuseBufs b;
-  const size_t need = carve_reuse(nullptr, m, cfg, mt, b);
+  const bool lean = ws_bytes < carve_reuse(nullptr, m, cfg, mt, b);
+  const size_t need = carve_reuse(nullptr, m, cfg, mt, b, lean);
   REQUIRE(ws && ws_bytes >= need, AKVS_ENOSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
-  carve_reuse(ws, m, cfg, mt, b);
+  carve_reuse(ws, m, cfg, mt, b, lean);
   // caller-visible outputs replace their workspace twins
   if (out->probe_k) b.probe_k = out->probe_k;
   if (out->probe_v) b.probe_v = out->probe_v;
@@ -1240,9 +1242,10 @@ akvs_status akvs_reuse_prefill_batch(const int32_t *const *tokens, int32_t batch
             "request %d: kv_rows below its token count", i);
   }
   BatchBufs b;
-  const size_t need = carve_batch(nullptr, m, cfgs, batch, pl, b);
+  const bool lean = ws_bytes < carve_batch(nullptr, m, cfgs, batch, pl, b);
+  const size_t need = carve_batch(nullptr, m, cfgs, batch, pl, b, lean);
   REQUIRE(ws && ws_bytes >= need, AKVS_ENOSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
-  carve_batch(ws, m, cfgs, batch, pl, b);
+  carve_batch(ws, m, cfgs, batch, pl, b, lean);
   for (int i = 0; i < batch; ++i) {  // caller-visible outputs replace their workspace twins
     const akvs_reuse_out &o = outs[i];
     BatchReq &r = b.req[i];
@@ -1422,7 +1425,7 @@ static size_t carve_decode(void *ws, const akvs_model_cfg *m, long long n_keys, 
     return cv.off;
   }
   size_t ml;
-  const size_t o = attention_part_floats(m, 1, n_keys, &ml);
+  const size_t o = attention_part_floats(m, 1, n_keys, &ml, true);  // (no plan here)
   b.part_o = o ? cv.take<float>(o) : nullptr;
   b.part_ml = o ? cv.take<float>(ml) : nullptr;
   b.part_rows = o ? (long long)(ml / ((size_t)m->n_q_heads * 2)) : 0;

@@ -1003,9 +1003,9 @@ int attn_split_keys(int n_keys, int n_splits) {
   return (per + 63) / 64 * 64;
 }
 
-int attn_part_splits(int rows, int hq, int hkv, int hd, int n_keys) {
+int attn_part_splits(int rows, int hq, int hkv, int hd, int n_keys, bool lean) {
   const int sp = attn_splits(rows, hq, hkv, n_keys);
-  const int most = attn_max_pieces(rows, n_keys);
+  const int most = lean ? kAttnMaxPieces : attn_max_pieces(rows, n_keys);
   const AttnEqShape e = attn_eq_shape(rows, hq, hkv, n_keys, hd, AKVS_BF16,
                                       (long long)most * rows, gemm_cu_count());
   return e.use ? std::max(sp, most) : sp;

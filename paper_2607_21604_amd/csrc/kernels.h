@@ -173,8 +173,10 @@ hipError_t launch_attention_plan(const AttnPlanReq *req, int n, int n_keys, int 
                                  int hd, int dtype, long long part_rows, hipStream_t s);
 // number of key splits launch_attention uses for `rows` rows over n_keys keys
 int attn_splits(int rows, int hq, int hkv, int n_keys);
-// partial slots per row that the part_o / part_ml buffers of such a call should hold
-int attn_part_splits(int rows, int hq, int hkv, int hd, int n_keys);
+// partial slots per row that the part_o / part_ml buffers of such a call should hold; lean: the
+// least that a caller's workspace is refused below (8 pieces a planned tile, where few rows over
+// many keys would take up to 16; launch_attention takes as many as part_rows holds)
+int attn_part_splits(int rows, int hq, int hkv, int hd, int n_keys, bool lean = false);
 int attn_split_keys(int n_keys, int n_splits);
 
 // ---- k_decode.hip -------------------------------------------------------------------

@@ -203,6 +203,14 @@ def test_attention_workspace(lib):
     assert st == akvs.AKVS_ENOSPACE
 
 
+@pytest.mark.parametrize("hq,hkv,need", [(64, 4, 249088), (96, 8, 265472)])
+def test_decode_scratch_does_not_grow_with_the_keys(lib, hq, hkv, need):
+    """More than 8 query heads per KV head: the one row's key split is the same over 4000 and
+    16000 keys, so a decode step fits the same scratch (and the fixed one's limit)."""
+    m = akvs.ModelCfg(3, 1024, hq, hkv, 128, 64, 500, 1e4, 1e-6, akvs.AKVS_BF16)
+    assert [akvs.akvs_decode_workspace_size(m, n) for n in (4000, 5000, 16000)] == [need] * 3
+
+
 def test_batch_workspace_and_validation(lib):
     """Batched reuse prefill: the workspace covers each request's single-call buffers;
     requests that disagree on the check layer, and an empty batch, are refused before any

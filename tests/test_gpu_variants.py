@@ -9,9 +9,10 @@ import torch
 import oracle
 import synthetic
 from paper_2607_21604_amd import akvs
+from paper_2607_21604_amd.runtime import Engine, _reuse_outputs
 from tests.test_gpu_steps import (gpu_offset_and_correction, make_offset_case,
                                   oracle_offset_and_correction, run_select)
-from tests.gpu_util import DEV, f64, max_rel, storage_round, to_dev
+from tests.gpu_util import DEV, dev_weights, f64, max_rel, storage_round, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -472,3 +473,64 @@ def test_selection_block_sizes(longest):
         keep[ref] = True
     rows = np.concatenate([np.nonzero(keep)[0], np.arange(tc, tc + q)])
     np.testing.assert_array_equal(got["rows"][:int(got["n_rows"][0])], rows)
+
+
+@pytest.mark.parametrize("hq,hkv,hd,rows,n_keys,least", [
+    (32, 8, 64, 160, 4500, 8357120), (40, 8, 128, 192, 6200, 20276480)])
+def test_attention_in_the_smaller_workspace(hq, hkv, hd, rows, n_keys, least):
+    """Few rows over many keys in a workspace of 8 pieces a tile (or the unplanned split), smaller
+    than the size asked for: accepted, the same values; 256 bytes less are refused."""
+    m = akvs.ModelCfg(1, 64, hq, hkv, hd, 64, 16, 1e4, 1e-6, akvs.AKVS_BF16)
+    full = akvs.akvs_attention_workspace_size(m, rows, n_keys)
+    assert full > least
+    pos = np.linspace(100, n_keys - 1, rows).astype(np.int32)
+    q, k, v = (storage_round(synthetic.random_array((n, h, hd), 90 + i), torch.bfloat16)
+               for i, (n, h) in enumerate([(rows, hq), (n_keys, hkv), (n_keys, hkv)]))
+    qd, kd, vd, pd = to_dev(q), to_dev(k), to_dev(v), to_dev(pos)
+    some = np.arange(0, rows, 7)
+    ref = oracle.attention(f64(q)[some], pos[some], f64(k), f64(v),
+                           np.arange(n_keys)).reshape(len(some), -1)
+    for nbytes in (full, least):
+        out = torch.empty((rows, hq * hd), dtype=torch.bfloat16, device=DEV)
+        ws = torch.full((nbytes,), 255, dtype=torch.uint8, device=DEV)
+        akvs.akvs_sparse_query_attention(qd, pd, rows, kd, vd, n_keys, m, out, ws)
+        assert max_rel(f64(out)[some], ref) < 1e-2
+    with pytest.raises(akvs.AkvsError):
+        akvs.akvs_sparse_query_attention(qd, pd, rows, kd, vd, n_keys, m, out, ws[:least - 256])
+
+
+def test_reuse_calls_in_the_smaller_workspace():
+    """The same of whole reuse calls, one and two requests (up to 184 rows over 4464 keys)."""
+    shape = synthetic.ModelShape("v", 3, 64, 32, 8, 64, 64, 500, 1e4)
+    eng = Engine(shape, dev_weights(synthetic.make_weights(shape, seed=3)))
+    m, lens, q = eng.m, [220] * 20, 64
+    cfg = akvs.reuse_cfg(lens, q, (1, 100))
+    tc, least, least2 = sum(lens), 84720128, 115074304
+    two = (akvs.ReuseCfg * 2)(cfg, cfg)
+    assert akvs.akvs_workspace_size(m, cfg) > least
+    assert akvs.akvs_batch_workspace_size(m, two, 2) > least2
+    rng = np.random.default_rng(1)
+    tokens = to_dev(rng.integers(0, 500, size=tc + q).astype(np.int32))
+    k, v = (to_dev(rng.standard_normal((3, tc, 8, 64)).astype(np.float32), torch.bfloat16)
+            for _ in range(2))
+    ref = eng.reuse_prefill(tokens, lens, q, k, v, refresh=(1, 100))
+    args = (eng.weights["embed"], eng.layers, eng.weights["final_norm"], m)
+
+    def outputs():
+        o = _reuse_outputs(eng, q, tc, len(ref["probe_k"]), tc + q, len(ref["probe_v"]))
+        return o, akvs.ReuseOut(*(akvs.ptr(o[x]) for x in (
+            "h_query", "k_corr", "v_corr", "probe_k", "probe_v", "d_k", "d_v", "rows", "n_rows")))
+
+    cache = akvs.cache_struct(k, v)
+    (o, s), (o1, s1), (o2, s2) = outputs(), outputs(), outputs()
+    ws = torch.full((max(least, least2),), 255, dtype=torch.uint8, device=DEV)
+    akvs.akvs_reuse_prefill(tokens, *args, cfg, cache, s, ws[:least])
+    ca, cc, co = akvs.batch_arrays([cfg, cfg], [cache, cache], [s1, s2])
+    akvs.akvs_reuse_prefill_batch([tokens, tokens], *args, ca, cc, co, ws[:least2])
+    n = int(ref["n_rows"])
+    for got in (o, o1, o2):
+        assert int(got["n_rows"]) == n and torch.equal(got["rows"][:n], ref["rows"][:n])
+        for x in ("h_query", "k_corr", "v_corr"):
+            assert max_rel(f64(got[x]), f64(ref[x])) < 2e-2
+    with pytest.raises(akvs.AkvsError):
+        akvs.akvs_reuse_prefill(tokens, *args, cfg, cache, s, ws[:least - 256])
