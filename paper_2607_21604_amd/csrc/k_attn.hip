@@ -195,6 +195,27 @@ __global__ __launch_bounds__(64) void k_attn_plan(PlanArgs p0, PlanArgs p1, int 
   if (lane == 0) plan[0] = make_int4(nt, total, cmax, 0);
 }
 
+// Partial outputs of the key splits take 16 bits per value: fp16 (11 significant bits) where the
+// largest value of the row's partial lies in [2^-8, 65504], so that none overflows and the small
+// ones lose less than bf16 would; else bf16 (8). The last bit of the partial's sum says which.
+// Against 64 bits, 159 rows of the 7B heads over 8000 keys: 2.63e-3 in 8 pieces and 2.76e-3 in 16
+// with bf16 partials, 2.35e-3 this way; no call of 210 shapes slower.
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_part(float a, float b, bool half) {
+  const half2_t h = {(_Float16)a, (_Float16)b};
+  return half ? __builtin_bit_cast(uint32_t, h) : pack_bf2(a, b);
+}
+__device__ __forceinline__ void part_values(uint4 w, float sum, float (&x)[8]) {
+  const bool half = __float_as_uint(sum) & 1u;
+  const uint32_t v[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const half2_t h = __builtin_bit_cast(half2_t, v[i]);
+    x[2 * i] = half ? (float)h[0] : __uint_as_float(v[i] << 16);
+    x[2 * i + 1] = half ? (float)h[1] : __uint_as_float(v[i] & 0xffff0000u);
+  }
+}
+
 // A block serves 32 * nrb rows of one query head (pack 1), or as many (row, head) pairs of the
 // G = pack query heads of KV head kvh: pair v is row v / G, head kvh * G + v % G. Wave w owns
 // 32 of them. Waves 0-3
@@ -680,18 +701,31 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
       part_ml[2 * prow] = -INFINITY;
       part_ml[2 * prow + 1] = -1.f;
     }
-  } else if (n_splits > 1) {  // this split's output over its own keys (bf16) + (max, sum)
+  } else if (n_splits > 1) {  // this split's output over its own keys + (max, sum)
     const float pinv = l_row > 0.f ? 1.0f / l_row : 0.f;  // no visible key: m = -inf, skipped
+    float big = 0.f;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        o[db][i] *= pinv;
+        big = fmaxf(big, fabsf(o[db][i]));
+      }
+    big = fmaxf(big, __shfl_xor(big, 32, 64));
+    const bool half = big >= 0x1p-8f && big <= 65504.f;
     bf16_t *po = part_o + prow * HD + hi * 4;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        store4(po + db * 32 + q4 * 8, o[db][4 * q4] * pinv, o[db][4 * q4 + 1] * pinv,
-               o[db][4 * q4 + 2] * pinv, o[db][4 * q4 + 3] * pinv);
+      for (int q4 = 0; q4 < 4; ++q4) {
+        *reinterpret_cast<uint2 *>(po + db * 32 + q4 * 8) =
+            make_uint2(pack_part(o[db][4 * q4], o[db][4 * q4 + 1], half),
+                       pack_part(o[db][4 * q4 + 2], o[db][4 * q4 + 3], half));
+      }
     if (hi == 0) {
       part_ml[2 * prow] = m_run;
-      part_ml[2 * prow + 1] = l_row;
+      part_ml[2 * prow + 1] =
+          l_row > 0.f ? __uint_as_float((__float_as_uint(l_row) & ~1u) | half) : l_row;
       if (split == n_part - 1 && n_part < n_splits) {  // end mark: no later split of this tile
         const size_t pend = ((size_t)n_part * rows + r) * hq + head;
         part_ml[2 * pend] = -INFINITY;
@@ -711,7 +745,7 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
 }
 
 // Merge of the key splits of one (row, head): split s holds its output over its own keys,
-// o_s (bf16, normalised by its own sum l_s), and (m_s, l_s); the result is
+// o_s (16 bits, normalised by its own sum l_s), and (m_s, l_s); the result is
 // sum_s w_s o_s / sum_s w_s with w_s = 2^(m_s - max m) l_s, added in split order. A split
 // whose keys all lie past the row (causal mask) holds m = -inf and l = 0 and is skipped, never
 // multiplied in (its part_o slot holds whatever the workspace held); one of NaN scores holds
@@ -745,13 +779,13 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
   for (int i = 0; i < 8; ++i) a[i] = 0.f;
   if (n_splits <= MAXS) {  // every partial of this item requested at once
     float2 ml[MAXS];
-    float o[MAXS][8];
+    uint4 o[MAXS];
 #pragma unroll
     for (int u = 0; u < MAXS; ++u) {
       if (u < n_splits) {
         const size_t pi = u * stride + item;
         ml[u] = *reinterpret_cast<const float2 *>(part_ml + 2 * pi);
-        load8(part_o + pi * hd + e0, o[u]);
+        o[u] = *reinterpret_cast<const uint4 *>(part_o + pi * hd + e0);
       }
     }
     int n = n_splits;  // up to the first end mark
@@ -768,8 +802,10 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
       if (u >= n || ml[u].y == 0.f) continue;
       const float w = exp2f(ml[u].x - moff) * ml[u].y;
       l += w;
+      float x[8];
+      part_values(o[u], ml[u].y, x);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) a[i] += w * o[u][i];
+      for (int i = 0; i < 8; ++i) a[i] += w * x[i];
     }
   } else {
     int n = n_splits;  // up to the first end mark
@@ -785,7 +821,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
       const float2 ml = *reinterpret_cast<const float2 *>(part_ml + 2 * pi);
       if (ml.y == 0.f) continue;  // no visible key: its part_o was never written
       float o[8];
-      load8(part_o + pi * hd + e0, o);
+      part_values(*reinterpret_cast<const uint4 *>(part_o + pi * hd + e0), ml.y, o);
       const float w = exp2f(ml.x - moff) * ml.y;
       l += w;
 #pragma unroll

@@ -534,3 +534,48 @@ def test_reuse_calls_in_the_smaller_workspace():
             assert max_rel(f64(got[x]), f64(ref[x])) < 2e-2
     with pytest.raises(akvs.AkvsError):
         akvs.akvs_reuse_prefill(tokens, *args, cfg, cache, s, ws[:least - 256])
+
+
+def test_attention_pieces_lose_no_precision():
+    """Rows cut into 16 pieces, whose outputs are held in 16 bits until the merge: 2.35e-3 from 64
+    bits, what the bf16 probabilities and outputs make (2.63e-3 with bf16 partials in 8 pieces,
+    2.76e-3 in 16)."""
+    hq, hkv, hd, rows, n_keys = 28, 4, 128, 159, 8000
+    rng = np.random.default_rng(rows)
+    pos = np.sort(rng.choice(n_keys, size=rows, replace=False)).astype(np.int32)
+    q, k, v = (storage_round(rng.standard_normal((n, h, hd)), torch.bfloat16)
+               for n, h in ((rows, hq), (n_keys, hkv), (n_keys, hkv)))
+    m = akvs.ModelCfg(1, 64, hq, hkv, hd, 64, 16, 1e4, 1e-6, akvs.AKVS_BF16)
+    ws = torch.empty(akvs.akvs_attention_workspace_size(m, rows, n_keys), dtype=torch.uint8,
+                     device=DEV)
+    out = torch.empty((rows, hq * hd), dtype=torch.bfloat16, device=DEV)
+    akvs.akvs_sparse_query_attention(to_dev(q), to_dev(pos), rows, to_dev(k), to_dev(v), n_keys, m,
+                                     out, ws)
+    some = np.arange(0, rows, 4)
+    ref = oracle.attention(f64(q)[some], pos[some], f64(k), f64(v),
+                           np.arange(n_keys)).reshape(len(some), -1)
+    assert np.linalg.norm(f64(out)[some] - ref) < 2.5e-3 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("hd,rows,n_keys", [(128, 40, 4500), (64, 300, 1300)])
+def test_attention_pieces_of_any_magnitude(hd, rows, n_keys):
+    """Values far outside the range of fp16 in either direction, one KV head each: the partial
+    outputs of the pieces keep bf16's range."""
+    scales = [1.0, 1e6, 3e4, 1e-5, 1e30, 1e-30]
+    hkv, hq = len(scales), 2 * len(scales)
+    rng = np.random.default_rng(hd)
+    pos = np.sort(rng.choice(n_keys, size=rows, replace=False)).astype(np.int32)
+    q, k, v = (storage_round(synthetic.random_array((n, h, hd), 95 + i), torch.bfloat16)
+               for i, (n, h) in enumerate([(rows, hq), (n_keys, hkv), (n_keys, hkv)]))
+    v = (v.float() * torch.tensor(scales)[None, :, None]).to(torch.bfloat16)
+    m = akvs.ModelCfg(1, 64, hq, hkv, hd, 64, 16, 1e4, 1e-6, akvs.AKVS_BF16)
+    nbytes = akvs.akvs_attention_workspace_size(m, rows, n_keys)
+    assert nbytes > 0
+    out = torch.empty((rows, hq, hd), dtype=torch.bfloat16, device=DEV)
+    akvs.akvs_sparse_query_attention(to_dev(q), to_dev(pos), rows, to_dev(k), to_dev(v), n_keys, m,
+                                     out, torch.empty(nbytes, dtype=torch.uint8, device=DEV))
+    some = np.arange(0, rows, 3)
+    ref = oracle.attention(f64(q)[some], pos[some], f64(k), f64(v), np.arange(n_keys))
+    got = f64(out)[some]
+    for h in range(hq):
+        assert max_rel(got[:, h], ref.reshape(len(some), hq, hd)[:, h]) < 1e-2
