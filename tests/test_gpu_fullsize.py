@@ -87,8 +87,8 @@ def test_fullsize_attention_sampled_rows():
 @pytest.mark.parametrize("rows_kind", ["probe", "all"])
 def test_fullsize_probe_layer_gemms_sampled_rows(rows_kind):
     """QKV projection and O-proj + MLP at the full 3B width, over M ~ 1400 probe-like rows
-    (the probe layers' GEMM shapes) and over all T = 4516 rows (the prefix layers'); the
-    two row counts take every block-tile shape of the projection GEMM between them. About
+    (the probe layers' GEMM shapes) and over all T = 4516 rows (the prefix layers'), on the
+    larger 8-wave tiles (the smaller ones and the few-row tiles have cases of their own). About
     40 sampled rows, the rows at tile edges among them, against the oracle."""
     pos = probe_like_positions(3) if rows_kind == "probe" else np.arange(T, dtype=np.int32)
     n = len(pos)

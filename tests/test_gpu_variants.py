@@ -92,6 +92,34 @@ def test_lm_head_rows(rows, vocab, d):
     assert torch.equal(only, toks)
 
 
+@pytest.mark.parametrize("rows", [2, 17, 32])
+@pytest.mark.parametrize("vocab", [152064, 131075])
+def test_lm_head_rows_of_large_vocabularies(vocab, rows):
+    """Vocabularies past 131072 rows, which take 80 of them per wave: the last blocks' remainders
+    of 320, rows past the vocabulary, picks there, with and without logits."""
+    d = 192
+    sh = synthetic.ModelShape("head", 1, d, 2, 2, 64, 128, vocab, 1e4)
+    m = akvs.model_cfg(sh)
+    h = torch.from_numpy(synthetic.random_array((rows, d), 13 + rows)).float()
+    w = torch.from_numpy(synthetic.random_array((vocab, d), 17) * 0.02).to(torch.bfloat16)
+    w[vocab - 1] = (h[0] / h[0].norm()).to(torch.bfloat16)  # row 0 picks the last
+    w[vocab - 3] = (h[1] / h[1].norm()).to(torch.bfloat16)
+    ref = f64(h) @ f64(w).T
+    bound = d * 2.0 ** -24 * (np.abs(f64(h)) @ np.abs(f64(w)).T)
+    hd, wd = to_dev(h), to_dev(w)
+    ws = torch.empty(akvs.akvs_decode_workspace_size(m, 0), dtype=torch.uint8, device=DEV)
+    logits = torch.full((rows, vocab), float("nan"), device=DEV)
+    toks = torch.full((rows,), -7, dtype=torch.int32, device=DEV)
+    akvs.akvs_lm_head(hd, rows, wd, m, logits, toks, ws)
+    got = f64(logits)
+    assert np.all(np.abs(got - ref) <= bound)
+    np.testing.assert_array_equal(toks.cpu().numpy(), got.argmax(axis=1))
+    assert toks[0].item() == vocab - 1 and toks[1].item() == vocab - 3
+    only = torch.full((rows,), -7, dtype=torch.int32, device=DEV)
+    akvs.akvs_lm_head(hd, rows, wd, m, None, only, ws)
+    assert torch.equal(only, toks)
+
+
 def test_lm_head_rows_infinities_and_nan():
     """Infinite weights and rows holding an infinity or a NaN: the values of the plain sums;
     NaN never wins the pick, a row of NaN picks nothing."""
@@ -371,8 +399,10 @@ def test_attention_pieces_keep_nan_scores():
     (320, 5, 1, 64, 448, 1), (320, 5, 1, 64, 448, 95), (320, 5, 1, 64, 448, 130),
     (64, 1, 1, 64, 64, 40)])
 def test_few_row_projections(d, hq, hkv, hd, ffn, rows):
-    """The few-row tiles at row, column and K remainders (K of 2176 and 320 are odd multiples of
-    64 or 128), with and without the K split, against the oracle; the same bits twice."""
+    """Few rows at row, column and K remainders (a K of 2176 is an odd multiple of 128), with and
+    without the K split, against the oracle; the same bits twice. The width-2048 to -4096 shapes
+    run on the few-row tiles (101 of akvs_projection_kernels and up), the last four, too small
+    for them, on the 128 x 128 8-wave tile."""
     shape = synthetic.ModelShape("v", 1, d, hq, hkv, hd, ffn, 64, 1e4)
     w = synthetic.make_weights(shape, seed=rows, embed=False)
     dims = oracle.dims_from(shape)
@@ -401,6 +431,28 @@ def test_few_row_projections(d, hq, hkv, hd, ffn, rows):
         assert max_rel(f64(got), ref) < 1e-2  # a bf16 rounding of inputs and outputs: 2^-8 each
     ref = oracle.model.output_and_mlp(h.astype(np.float64), f64(att), sw, dims)
     assert max_rel(f64(runs[0][3]), ref) < 1e-2
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,ffn,rows,codes", [
+    (512, 32, 8, 64, 1024, 200, (111, 104, 101, 101)),    # heads of 64 on 64 x 64,
+    (512, 32, 8, 64, 1024, 385, (121, 101, 111, 101)),    # 96 x 64
+    (1024, 32, 8, 64, 1024, 501, (131, 101, 111, 101)),   # and 96 x 128 tiles
+    (512, 8, 2, 64, 1088, 1, (101, 101, 101, 131)),       # 17 k-tiles of 64
+    (1088, 8, 2, 64, 2176, 499, (131, 111, 131, 111)),
+    (512, 8, 2, 64, 4160, 97, (101, 101, 205, 138)),      # 65 k-tiles in 8 slices, 96 x 128
+    (3072, 8, 2, 64, 4160, 97, (306, 101, 303, 148)),     # and 128 x 128; 8-wave K splits
+    (512, 24, 8, 128, 1024, 201, (121, 118, 101, 101)),
+    (512, 8, 2, 64, 4160, 901, (111, 101, 201, 136)),     # the 8-wave tiles: 192 x 256,
+    (512, 8, 2, 64, 4160, 701, (111, 101, 202, 138)),     # 256 x 128,
+    (512, 8, 2, 64, 4160, 385, (101, 101, 203, 138)),     # 192 x 128,
+    (512, 8, 2, 64, 18944, 97, (101, 101, 204, 108)),     # 128 x 256
+    (512, 8, 2, 64, 8192, 897, (111, 101, 200, 312))])    # and 256 x 256
+def test_bf16_projection_kernels(d, hq, hkv, hd, ffn, rows, codes):
+    """Each few-row and 8-wave tile, named by akvs_projection_kernels, at remainders of rows,
+    columns and k-tiles, against the oracle (a bf16 rounding of inputs and outputs)."""
+    shape = synthetic.ModelShape("v", 1, d, hq, hkv, hd, ffn, 64, 1e4)
+    assert akvs.akvs_projection_kernels(akvs.model_cfg(shape), rows) == codes
+    _check_projections(shape, rows, 1e-2)
 
 
 @pytest.mark.parametrize("hq,hkv,hd,rows,n_keys", [
