@@ -16,14 +16,19 @@
 // operand), so a lane holds four neighbouring output columns of one row and the epilogues
 // work from the registers: a tile's columns are pairs (gate / up, the two rotary halves)
 // stacked so that a wave holds both members.
-// What bounds it: from about 150 rows on the operand traffic from L2 into the CUs (12 to 16 TB/s
-// at the tiles' (BM + BN) x 128 bytes per 64 columns), below that the weights' stream and the
-// launch. 3B QKV, output, gate/up and down projections, 8-wave tiles with their K split before:
-// 64 rows 21.1, 17.2, 37.8, 25.6 us -> 12.2, 10.6, 22.9, 17.0; 173 rows 24.3, 18.4, 39.8, 29.7
-// -> 15.7, 15.1, 34.6, 24.1; 475 rows 32.0, 25.5, 52.2, 41.8 -> 28.5, 19.0, 54.7, 41.5 (gate/up
-// stays on the 8-wave tiles there). Stages: 64 x 64 tiles of 64 columns three deep took 22.1 us
-// for the 173-row QKV, eight deep 17.2, and with the fragments of two tiles in registers 16.4;
-// 128 columns four deep 15.7.
+// What bounds it: below about 150 rows the weights' stream and the launch, from there the
+// k-steps, whose operands pass from L2 to the CUs at 12 to 16 TB/s (the tiles' (BM + BN) x 128
+// bytes per 64 columns); whether that rate is the limit or the LDS traffic at one wave per SIMD
+// has not been told apart.
+// us of the 3B QKV, output, gate/up and down projections, 8-wave tiles with their K split -> the
+// picks of launch_gemm (tile, K slices), weights from HBM:
+//    64 rows  21.8, 18.7, 38.2, 27.2 -> 15.8 (32x64), 13.0 (64x64, 4), 27.2 (64x64), 22.0 (64x64, 4)
+//   173 rows  22.9, 20.3, 41.2, 28.4 -> 19.4 (64x64), 17.9 (96x128, 5), 37.5 (96x128), 27.5 (96x128, 5)
+// and with the weights in cache, as in a repeated call, at 173 rows 20.9, 19.6, 38.4, 28.4 ->
+// 15.6, 16.2, 25.1, 22.0 (the output projection on 64x64 without slices 13.8, but 18.7 from HBM). At
+// 475 rows only the output projection is taken: 26.7 -> 23.4 (96x64).
+// Stages: 64 x 64 tiles of 64 columns three deep took 22.1 us for the 173-row QKV, eight deep
+// 17.2, and with the fragments of two tiles in registers 16.4; 128 columns four deep 15.7.
 #include <algorithm>
 
 #include "gemm_dev.h"
@@ -393,14 +398,21 @@ static void launch_few_tile(const void *A, int lda, const void *B, int ldb, int 
 hipError_t launch_few(int tile, int splits, const void *A, int lda, const void *B, int ldb, int M,
                       int N, int K, const int32_t *m_dev, const Epi &e, float *part,
                       hipStream_t s) {
+#define AKVS_FEW_TILE(T, NST)                                                              \
+  case T:                                                                                  \
+    launch_few_tile<kFewTiles[T].bm, kFewTiles[T].bn, kFewTiles[T].bk, NST>(               \
+        A, lda, B, ldb, M, N, K, m_dev, e, splits, part, s);                               \
+    break
+  static_assert(kFewCount == 5, "a case per tile");
   switch (tile) {
-    case 0: launch_few_tile<32, 64, 128, 6>(A, lda, B, ldb, M, N, K, m_dev, e, splits, part, s); break;
-    case 1: launch_few_tile<64, 64, 128, 4>(A, lda, B, ldb, M, N, K, m_dev, e, splits, part, s); break;
-    case 2: launch_few_tile<96, 64, 128, 4>(A, lda, B, ldb, M, N, K, m_dev, e, splits, part, s); break;
-    case 3: launch_few_tile<96, 128, 64, 4>(A, lda, B, ldb, M, N, K, m_dev, e, splits, part, s); break;
-    case 4: launch_few_tile<128, 128, 64, 4>(A, lda, B, ldb, M, N, K, m_dev, e, splits, part, s); break;
+    AKVS_FEW_TILE(0, 6);
+    AKVS_FEW_TILE(1, 4);
+    AKVS_FEW_TILE(2, 4);
+    AKVS_FEW_TILE(3, 4);
+    AKVS_FEW_TILE(4, 4);
     default: return hipErrorInvalidValue;
   }
+#undef AKVS_FEW_TILE
   return hipGetLastError();
 }
 

@@ -2,15 +2,16 @@
 // epilogues: RoPE + q/k/v split (QKV), residual add into the fp32 stream (RESID),
 // SiLU(gate) * up (SWIGLU) and plain stores.
 //
-// bf16 path, four kernels on v_mfma_f32_32x32x16_bf16 with fp32 accumulation, operand
-// tiles double-buffered in LDS and fed by register stages of global loads:
+// bf16 path, fp32 accumulation on the matrix cores. Three kernels on v_mfma_f32_32x32x16_bf16,
+// operand tiles double-buffered in LDS and fed by register stages of global loads:
 //   k_gemm_bf16_w8 - 8 waves, BM x BN x 64 tiles (256/192/128 x 256/128), all waves on one
 //                    schedule interleaving loads, LDS stores and MFMAs;
 //   k_gemm_bf16_pp - 8 waves, 192 x 256 tiles, two wave groups alternating memory and
 //                    MFMA phases ("ping-pong");
-//   k_gemm_few     - few rows (k_few.hip): small tiles, operands straight into LDS;
-//   k_gemm_bf16    - 4 waves, 128 x 128 tiles, with the K split (and its fixup pass) for
-//                    grids too small to fill the GPU and for operands past 2 GiB.
+//   k_gemm_bf16    - 4 waves, 128 x 128 tiles, with the K split (and its fixup pass), for
+//                    operands past 2 GiB.
+// And for few rows k_gemm_few (k_few.hip): small tiles on v_mfma_f32_16x16x32_bf16, operands
+// straight from memory into LDS.
 // launch_gemm picks the tile per launch from the row count (on the device when only the device
 // knows it: k_gemm_bf16_pick runs the chosen kernel's blocks). In every kernel the
 // accumulator tile is staged through LDS so the epilogues can pair columns (rotary halves,
@@ -1304,20 +1305,12 @@ static W8Choice w8_choice(int M, int N, int K, const int32_t *m_dev, int mode,
 // tile's measured step time; it cannot be shorter than its weights' stream (5.3 TB/s for the
 // few-row kernels' deep request queue, 4.4 over several rounds of them, 4.2 for the 8-wave
 // tiles, 5.3 for 128 x 256, 3.6 when they split K).
-// A K split adds a second launch and the partials' round trip. Examples at 173 rows of the
-// 3B shapes, 8-wave against few-row: QKV 24.3 -> 15.8 us (64 x 64), output 18.4 -> 13.3
-// (64 x 64), gate/up 39.8 -> 34.0 (96 x 128), down 29.7 -> 25.3 (96 x 128, four slices); at
-// 64 rows 21.1 -> 12.2, 17.2 -> 10.0, 37.8 -> 22.8 and 25.6 -> 16.6. From about 500 rows on the
-// 8-wave tiles take over (3B gate/up at 475 rows: 52 against 66 us).
-struct FewTile {
-  int bm, bn, bk;
-  float step;  // us per 64 columns of K, chip full
-};
-constexpr FewTile kFewTiles[] = {
-    {32, 64, 128, 0.20f}, {64, 64, 128, 0.29f}, {96, 64, 128, 0.33f}, {96, 128, 64, 0.56f},
-    {128, 128, 64, 0.65f}};
-constexpr int kFewCount = 5;
-constexpr int kFewMaxRows = 1024;  // the range the step times were measured on
+// A K split adds a second launch and the partials' round trip. (What the picks measured stands
+// with the kernel; against 8-wave tiles alone, 240 calls over the projections of six models at 1
+// to 2100 rows took 1.16x less on average, and none that is picked another kernel 4 % more.)
+constexpr float kFewStep[kFewCount] = {  // us per 64 columns of K of each tile, chip full
+    0.20f, 0.29f, 0.33f, 0.56f, 0.65f};
+constexpr int kFewMaxRows = 1024;  // (step times from 24 to 820 rows, picks checked up to here)
 
 struct FewChoice {
   int tile;  // -1: the 8-wave kernels
@@ -1362,8 +1355,9 @@ static FewChoice few_choice(int M, int N, int K, const int32_t *m_dev, const Epi
       t_best += 4 + std::max((double)cost * (1.70 / 65536) * nk64, w_mb / (w8 == 4 ? 5.3 : 4.2));
     }
   }
-  // estimates closer than 6 % do not tell which is faster (picked at 2 and 5 %: the projections of
-  // a 32B layer at 174 rows 302 us, 289 on the 8-wave tiles; of a 3B layer at 518 rows 178 and 171)
+  // closer estimates do not tell which is faster: taken at an estimated gain of 2 and 5 %, the
+  // projections of a 32B layer at 174 rows took 302 us against 289 on the 8-wave tiles, of a 3B
+  // layer at 518 rows 178 against 171; at 6 % no shape of the 240 above lost
   t_best *= 0.94;
   for (int i = 0; i < kFewCount; ++i) {
     const FewTile &t = kFewTiles[i];
@@ -1386,7 +1380,7 @@ static FewChoice few_choice(int M, int N, int K, const int32_t *m_dev, const Epi
       for (int p = 0; p < n_pts; ++p) {
         const int m = pts[p], tiles = ((m + t.bm - 1) / t.bm) * n_cols;
         const double rounds = (tiles * sp + cus - 1) / cus;
-        us += 4 + std::max(rounds * steps * t.step, w_mb / (rounds > 1 ? 4.4 : 5.3)) +
+        us += 4 + std::max(rounds * steps * kFewStep[i], w_mb / (rounds > 1 ? 4.4 : 5.3)) +
               (sp > 1 ? split_cost((double)sp * m * N) : 0.0);
       }
       if (us < t_best) {

@@ -135,8 +135,14 @@ size_t gemm_part_floats(int M, int N, int K, int mode);
 // of A and B dense).
 int gemm_kernel_of(int M, int N, int K, int dtype, const Epi &epi, const float *part);
 // ---- k_few.hip ----------------------------------------------------------------------
-// The few-row GEMM with tile `tile` of few_tile (k_gemm.hip picks it); splits > 1: RESID only,
+// The few-row GEMM with tile `tile` of kFewTiles (k_gemm.hip picks it); splits > 1: RESID only,
 // partials to part [splits][M][N], added to the residual by launch_few_sum.
+struct FewTile {
+  int bm, bn, bk;
+};
+constexpr FewTile kFewTiles[] = {
+    {32, 64, 128}, {64, 64, 128}, {96, 64, 128}, {96, 128, 64}, {128, 128, 64}};
+constexpr int kFewCount = sizeof(kFewTiles) / sizeof(kFewTiles[0]);
 constexpr int kFewMaxSplits = 8;
 hipError_t launch_few(int tile, int splits, const void *A, int lda, const void *B, int ldb, int M,
                       int N, int K, const int32_t *m_dev, const Epi &e, float *part,
