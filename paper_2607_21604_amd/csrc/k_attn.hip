@@ -195,18 +195,19 @@ __global__ __launch_bounds__(64) void k_attn_plan(PlanArgs p0, PlanArgs p1, int 
   if (lane == 0) plan[0] = make_int4(nt, total, cmax, 0);
 }
 
-// Partial outputs of the key splits take 16 bits per value: fp16 (11 significant bits) where the
+// Partial outputs of the key splits take 16 bits per value: bf16 (8 significant bits), but in a plan
+// of packed heads or more than 8 pieces, which rounds more of a row's terms, fp16 (11) where the
 // largest value of the row's partial lies in [2^-8, 65504], so that none overflows and the small
-// ones lose less than bf16 would; else bf16 (8). The last bit of the partial's sum says which.
-// Against 64 bits, 159 rows of the 7B heads over 8000 keys: 2.63e-3 in 8 pieces and 2.76e-3 in 16
+// ones lose less than in bf16; the last bit of such a partial's sum says which. Against 64 bits,
+// 159 rows of the 7B heads over 8000 keys: 2.63e-3 in 8 pieces one by one, 2.76e-3 packed in 16
 // with bf16 partials, 2.35e-3 this way; no call of 210 shapes slower.
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_part(float a, float b, bool half) {
   const half2_t h = {(_Float16)a, (_Float16)b};
   return half ? __builtin_bit_cast(uint32_t, h) : pack_bf2(a, b);
 }
-__device__ __forceinline__ void part_values(uint4 w, float sum, float (&x)[8]) {
-  const bool half = __float_as_uint(sum) & 1u;
+__device__ __forceinline__ void part_values(uint4 w, bool halves, float sum, float (&x)[8]) {
+  const bool half = halves && (__float_as_uint(sum) & 1u);
   const uint32_t v[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
                                                    const int32_t *rows_dev,
                                                    const bf16_t *__restrict__ Kc,
                                                    const bf16_t *__restrict__ Vc, int n_keys,
-                                                   int hq, int hkv, int pack,
+                                                   int hq, int hkv, int pack, bool halves,
                                                    int nrb, int n_tiles, int n_splits,
                                                    int split_keys,
                                                    float scale_log2,
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
         big = fmaxf(big, fabsf(o[db][i]));
       }
     big = fmaxf(big, __shfl_xor(big, 32, 64));
-    const bool half = big >= 0x1p-8f && big <= 65504.f;
+    const bool half = halves && big >= 0x1p-8f && big <= 65504.f;
     bf16_t *po = part_o + prow * HD + hi * 4;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -725,7 +726,7 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t *__restrict__ Q,
     if (hi == 0) {
       part_ml[2 * prow] = m_run;
       part_ml[2 * prow + 1] =
-          l_row > 0.f ? __uint_as_float((__float_as_uint(l_row) & ~1u) | half) : l_row;
+          halves && l_row > 0.f ? __uint_as_float((__float_as_uint(l_row) & ~1u) | half) : l_row;
       if (split == n_part - 1 && n_part < n_splits) {  // end mark: no later split of this tile
         const size_t pend = ((size_t)n_part * rows + r) * hq + head;
         part_ml[2 * pend] = -INFINITY;
@@ -763,7 +764,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
                                                       const int32_t *rows_dev, int hq, int hd,
                                                       bf16_t *__restrict__ out,
                                                       const int32_t *row_base,
-                                                      const int4 *plan) {
+                                                      const int4 *plan, bool halves) {
   const int per = hd >> 3;  // threads per (row, head)
   const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long item = gid / per;
@@ -803,7 +804,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
       const float w = exp2f(ml[u].x - moff) * ml[u].y;
       l += w;
       float x[8];
-      part_values(o[u], ml[u].y, x);
+      part_values(o[u], halves, ml[u].y, x);
 #pragma unroll
       for (int i = 0; i < 8; ++i) a[i] += w * x[i];
     }
@@ -821,7 +822,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(const bf16_t *__restrict__
       const float2 ml = *reinterpret_cast<const float2 *>(part_ml + 2 * pi);
       if (ml.y == 0.f) continue;  // no visible key: its part_o was never written
       float o[8];
-      part_values(*reinterpret_cast<const uint4 *>(part_o + pi * hd + e0), ml.y, o);
+      part_values(*reinterpret_cast<const uint4 *>(part_o + pi * hd + e0), halves, ml.y, o);
       const float w = exp2f(ml.x - moff) * ml.y;
       l += w;
 #pragma unroll
@@ -1094,12 +1095,13 @@ hipError_t launch_attention(const void *q, const int32_t *pos, int pos0, int row
       n_tiles = (rows + 32 * nrb - 1) / (32 * nrb);
       blocks = n_tiles * hq * n_splits;
     }
+    const bool halves = planned && (pack > 1 || n_splits > kAttnMaxPieces);  // (see pack_part)
     const dim3 g(blocks), b(64 * nrb);
     const int4 *P = planned ? reinterpret_cast<const int4 *>(plan) : nullptr;
 #define AKVS_ATTN(HD_, PREF_)                                                                    \
   hipLaunchKernelGGL((k_attn_bf16<HD_, PREF_>), g, b, 0, s, Q, pos, pos0, rows, rows_dev, K, V,    \
-                     n_keys, hq, hkv, pack, nrb, n_tiles, n_splits, split_keys, scale_log2, O,     \
-                     reinterpret_cast<bf16_t *>(part_o), part_ml, row_base, P)
+                     n_keys, hq, hkv, pack, halves, nrb, n_tiles, n_splits, split_keys,            \
+                     scale_log2, O, reinterpret_cast<bf16_t *>(part_o), part_ml, row_base, P)
     if (hd == 128) {
       AKVS_ATTN(128, false);  // the direct-to-LDS staging, 4- and 8-wave blocks alike
     } else {
@@ -1113,10 +1115,10 @@ hipError_t launch_attention(const void *q, const int32_t *pos, int pos0, int row
       const bf16_t *po = reinterpret_cast<const bf16_t *>(part_o);
       if (n_splits <= 8)
         hipLaunchKernelGGL((k_attn_combine<8>), gc, bc, 0, s, po, part_ml, n_splits, rows, rows_dev,
-                           hq, hd, O, row_base, P);
+                           hq, hd, O, row_base, P, halves);
       else
         hipLaunchKernelGGL((k_attn_combine<16>), gc, bc, 0, s, po, part_ml, n_splits, rows,
-                           rows_dev, hq, hd, O, row_base, P);
+                           rows_dev, hq, hd, O, row_base, P, halves);
     }
   } else {
     const float scale = 1.4426950408889634f / sqrtf((float)hd);
