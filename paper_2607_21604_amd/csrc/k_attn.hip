@@ -986,15 +986,25 @@ __global__ __launch_bounds__(512) void k_attn_f32(const float *__restrict__ Q, c
     for (int c = 0; c < HD / 64; ++c) nan |= so[c] != so[c];
     if (__ballot(nan && sl == sl) != 0) {
       // NaN over a sum that is none: an infinite or NaN value. It may be that of a key which
-      // another row of the block sees and this one does not (its p of 0 makes NaN of it too),
-      // so the row is formed again over its own keys, a lane per key for the scores.
-      const int end = __shfl(lim, i, 64);
+      // another row of the block sees and this one does not (its p of 0 makes NaN of it too), or
+      // of the block's last key, which masked keys re-read: if there is one, the row is formed
+      // again over its own keys, a lane per key for the scores.
+      const int end = __shfl(lim, i, 64), far = __shfl(last, 0, 64);
+      float odd = 0.f;  // NaN once a hidden value is infinite or NaN
+      for (int k = max(min(end + 1, far), 0); k <= far; ++k) {
+        const float *v = Vc + ((size_t)k * hkv + kvh) * HD + lane;
+#pragma unroll
+        for (int c = 0; c < HD / 64; ++c) odd = fmaf(v[64 * c], 0.f, odd);
+      }
+      const bool again = __ballot(odd != 0.f) != 0;
       const float *q = Q + ((size_t)(row0 + i) * hq + head) * HD;
       float rm = -INFINITY;
-      sl = 0.f;
+      if (again) {
+        sl = 0.f;
 #pragma unroll
-      for (int c = 0; c < HD / 64; ++c) so[c] = 0.f;
-      for (int k0 = 0; k0 <= end; k0 += 64) {
+        for (int c = 0; c < HD / 64; ++c) so[c] = 0.f;
+      }
+      for (int k0 = 0; again && k0 <= end; k0 += 64) {
         const float *k = Kc + ((size_t)min(k0 + lane, end) * hkv + kvh) * HD;
         f32x4_t s4 = zero;
         for (int d = 0; d < HD; d += 4)

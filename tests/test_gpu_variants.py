@@ -345,6 +345,25 @@ def test_fp32_attention_hidden_values_stay_hidden(hd, pos, key, bad):
     np.testing.assert_array_equal(got[~fin], ref[~fin])
 
 
+def test_fp32_attention_seen_nan_costs_nothing():
+    """A NaN value that every row sees is no reason to form the rows again: the call takes its
+    usual time."""
+    hq, hkv, hd, rows, n_keys = 8, 2, 128, 1000, 2000
+    m = akvs.ModelCfg(1, 64, hq, hkv, hd, 64, 16, 1e4, 1e-6, akvs.AKVS_F32)
+    q, k, v = (torch.randn((n, h, hd), device=DEV) for n, h in ((rows, hq), (n_keys, hkv),
+                                                                (n_keys, hkv)))
+    pos = torch.arange(n_keys - rows, n_keys, dtype=torch.int32, device=DEV)
+    out = torch.empty((rows, hq * hd), device=DEV)
+    us = []
+    for _ in range(2):
+        us.append(_gpu_us(lambda: akvs.akvs_sparse_query_attention(q, pos, rows, k, v, n_keys, m,
+                                                                   out)))
+        v[3, :, 7] = float("nan")
+    assert us[1] < 2 * us[0], us
+    nan = torch.isnan(out.view(rows, hq, hd))
+    assert nan[:, :, 7].all() and int(nan.sum()) == rows * hq
+
+
 @pytest.mark.parametrize("hd,pos,key", [
     (64, np.arange(40), 16), (128, np.arange(40), 32),    # alone in its wave's share of a row
     (128, np.arange(0, 300, 3), 144), (64, np.array([127, 128, 129]), 128),
